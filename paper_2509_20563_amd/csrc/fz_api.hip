@@ -1333,25 +1333,49 @@ void init_params(float* w, uint64_t seed) {
     }
 }
 
+// Device memory of one training call: one allocation (each costs the call
+// tens of microseconds), freed with the call.
 struct TrainBufs {
+    uint8_t* base = nullptr;
     TrainScratch s = {};
     float *w = nullptr, *m = nullptr, *v = nullptr, *tgt = nullptr, *loss = nullptr;
     uint32_t* idx = nullptr;
+    hipEvent_t copied[2] = {};
     ~TrainBufs() {
-        float* fs[] = {s.Z, s.H1, s.H2, s.DY, s.DH1, s.DH2, s.SE, s.grad, w, m, v, tgt, loss};
-        for (float* f : fs) hipFree(f);
-        hipFree(idx);
+        hipFree(base);
+        for (hipEvent_t e : copied)
+            if (e) hipEventDestroy(e);
     }
-    bool alloc_batch(uint32_t B) {
-        return hipMalloc((void**)&s.Z, sizeof(float) * B * kNFeat) == hipSuccess &&
-               hipMalloc((void**)&s.H1, sizeof(float) * B * kNHid) == hipSuccess &&
-               hipMalloc((void**)&s.H2, sizeof(float) * B * kNHid) == hipSuccess &&
-               hipMalloc((void**)&s.DY, sizeof(float) * B * kNOut) == hipSuccess &&
-               hipMalloc((void**)&s.DH1, sizeof(float) * B * kNHid) == hipSuccess &&
-               hipMalloc((void**)&s.DH2, sizeof(float) * B * kNHid) == hipSuccess &&
-               hipMalloc((void**)&s.SE, sizeof(float) * B) == hipSuccess &&
-               hipMalloc((void**)&s.grad, sizeof(float) * kSelectorParams) == hipSuccess &&
-               hipMalloc((void**)&w, sizeof(float) * kSelectorParams) == hipSuccess;
+    // scratch of a batch of B; with n the moments, targets and order of n
+    // samples and the losses of `epochs` epochs too
+    bool alloc(uint32_t B, uint64_t n, uint32_t epochs) {
+        uint64_t at = 0;
+        auto take = [&](uint64_t bytes) {
+            const uint64_t o = at;
+            at += (bytes + 255) & ~255ull;
+            return o;
+        };
+        const uint64_t row = sizeof(float) * kTrainRow;
+        const uint64_t ow = take(kTrainWBytes), og = take(row), oz = take(row * train_rows(B)),
+                       ol = take(sizeof(double) * (epochs ? epochs : 1));
+        const uint64_t om = n ? take(row) : 0, ov = n ? take(row) : 0, ot = n ? take(sizeof(float) * 3 * n) : 0,
+                       oi = n ? take(sizeof(uint32_t) * n) : 0;
+        if (hipMalloc((void**)&base, at) != hipSuccess) return false;
+        w = (float*)(base + ow);
+        s.grad = (float*)(base + og);
+        s.Z = (float*)(base + oz);
+        if (n) {
+            s.loss_sum = (double*)(base + ol);
+            m = (float*)(base + om);
+            v = (float*)(base + ov);
+            tgt = (float*)(base + ot);
+            idx = (uint32_t*)(base + oi);
+            for (hipEvent_t& e : copied)
+                if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) return false;
+        } else {
+            loss = (float*)(base + ol);
+        }
+        return true;
     }
 };
 
@@ -1369,59 +1393,71 @@ int fz_selector_train(fz_ctx* c, const float* d_feat, const uint32_t* d_costs, u
     hipStream_t st = (hipStream_t)stream;
     const uint32_t B = (uint32_t)(tp->batch < n ? tp->batch : n);
     const uint64_t nbatch = (n + B - 1) / B;
+    // losses come back once for every kLossEpochs epochs, so that the host's
+    // shuffle of the next epoch runs while the device trains on this one
+    constexpr uint32_t kLossEpochs = 1024;
+    const uint32_t lcap = tp->epochs < kLossEpochs ? tp->epochs : kLossEpochs;
     TrainBufs tb;
-    if (!tb.alloc_batch(B) || hipMalloc((void**)&tb.m, sizeof(float) * kSelectorParams) != hipSuccess ||
-        hipMalloc((void**)&tb.v, sizeof(float) * kSelectorParams) != hipSuccess ||
-        hipMalloc((void**)&tb.tgt, sizeof(float) * 3 * n) != hipSuccess ||
-        hipMalloc((void**)&tb.loss, sizeof(float) * nbatch) != hipSuccess ||
-        hipMalloc((void**)&tb.idx, sizeof(uint32_t) * n) != hipSuccess)
-        return FZ_ERR_NOMEM;
+    if (!tb.alloc(B, n, lcap)) return FZ_ERR_NOMEM;
     float* hw = (float*)malloc(sizeof(float) * kSelectorParams);
-    uint32_t* perm = (uint32_t*)malloc(sizeof(uint32_t) * n);
-    float* hl = (float*)malloc(sizeof(float) * nbatch);
-    int rc = (hw && perm && hl) ? FZ_OK : FZ_ERR_NOMEM;
+    // the order of an epoch is shuffled in one buffer while the previous
+    // epoch's may still be read from the other
+    uint32_t* perm[2] = {(uint32_t*)malloc(sizeof(uint32_t) * n), (uint32_t*)malloc(sizeof(uint32_t) * n)};
+    double* hl = (double*)malloc(sizeof(double) * lcap);
+    int rc = (hw && perm[0] && perm[1] && hl) ? FZ_OK : FZ_ERR_NOMEM;
     if (rc == FZ_OK) {
         init_params(hw, tp->seed);
         bool ok = hipMemcpyAsync(tb.w, hw, sizeof(float) * kSelectorParams, hipMemcpyHostToDevice, st) == hipSuccess;
-        launch_fill32(st, (uint32_t*)tb.m, kSelectorParams, 0);
-        launch_fill32(st, (uint32_t*)tb.v, kSelectorParams, 0);
+        launch_fill32(st, (uint32_t*)tb.m, kTrainRow, 0);
+        launch_fill32(st, (uint32_t*)tb.v, kTrainRow, 0);
         launch_targets(st, d_costs, n, tb.tgt);
         launch_feature_stats(st, d_feat, n, tb.w);
-        for (uint64_t i = 0; i < n; i++) perm[i] = (uint32_t)i;
+        double* const loss0 = tb.s.loss_sum;
+        tb.s.adam = TrainAdam{tb.w, tb.m, tb.v, tp->lr, tp->beta1, tp->beta2, tp->eps, 0};
+        for (uint64_t i = 0; i < n; i++) perm[0][i] = (uint32_t)i;
         uint64_t rs = tp->seed ^ 0x5DEECE66Dull;
-        int step = 0;
         for (uint32_t e = 0; ok && e < tp->epochs; e++) {
+            uint32_t* p = perm[e & 1];
+            if (e >= 2) ok = hipEventSynchronize(tb.copied[e & 1]) == hipSuccess;
+            if (e) memcpy(p, perm[(e + 1) & 1], sizeof(uint32_t) * n);
             // Fisher-Yates shuffle of the sample order
             for (uint64_t i = n - 1; i > 0; i--) {
                 const uint64_t j = splitmix64(rs) % (i + 1);
-                const uint32_t t = perm[i];
-                perm[i] = perm[j];
-                perm[j] = t;
+                const uint32_t t = p[i];
+                p[i] = p[j];
+                p[j] = t;
             }
-            ok = hipMemcpyAsync(tb.idx, perm, sizeof(uint32_t) * n, hipMemcpyHostToDevice, st) == hipSuccess;
+            ok = ok && hipMemcpyAsync(tb.idx, p, sizeof(uint32_t) * n, hipMemcpyHostToDevice, st) == hipSuccess &&
+                 hipEventRecord(tb.copied[e & 1], st) == hipSuccess;
+            const uint32_t le = e % kLossEpochs;
+            if (le == 0) launch_fill32(st, (uint32_t*)loss0, 2 * (uint64_t)lcap, 0);
+            tb.s.loss_sum = loss0 + le;
             for (uint64_t bi = 0; ok && bi < nbatch; bi++) {
                 const uint64_t start = bi * B;
                 const uint32_t nb = (uint32_t)(n - start < B ? n - start : B);
-                launch_train_batch(st, tb.w, d_feat, tb.tgt, tb.idx + start, nb, tb.s, tb.loss + bi);
-                launch_adam(st, tb.w, tb.m, tb.v, tb.s.grad, ++step, tp->lr, tp->beta1, tp->beta2, tp->eps);
+                tb.s.adam.t++;
+                launch_train_batch(st, tb.w, d_feat, tb.tgt, tb.idx + start, nb, tb.s, nullptr);
             }
-            ok = ok && hipMemcpyAsync(hl, tb.loss, sizeof(float) * nbatch, hipMemcpyDeviceToHost, st) == hipSuccess &&
-                 hipStreamSynchronize(st) == hipSuccess;
-            if (ok && h_loss) {
-                double a = 0.0;
-                for (uint64_t bi = 0; bi < nbatch; bi++) a += hl[bi];
-                h_loss[e] = (float)(a / (double)nbatch);
+            if (ok && (le + 1 == lcap || e + 1 == tp->epochs)) {
+                ok = hipMemcpyAsync(hl, loss0, sizeof(double) * (le + 1), hipMemcpyDeviceToHost, st) == hipSuccess &&
+                     hipStreamSynchronize(st) == hipSuccess;
+                for (uint32_t k = 0; ok && h_loss && k <= le; k++) h_loss[e - le + k] = (float)(hl[k] / (double)nbatch);
             }
         }
         ok = ok && hipMemcpyAsync(hw, tb.w, sizeof(float) * kSelectorParams, hipMemcpyDeviceToHost, st) == hipSuccess &&
              hipStreamSynchronize(st) == hipSuccess && hipGetLastError() == hipSuccess;
-        if (!ok) rc = FZ_ERR_HIP;
+        if (!ok) {
+            // copies from the host buffers freed below may still be running
+            hipStreamSynchronize(st);
+            rc = FZ_ERR_HIP;
+        }
         for (int i = 0; rc == FZ_OK && i < kSelectorParams; i++)
             if (!__builtin_isfinite(hw[i])) rc = FZ_ERR_INTERNAL;
         if (rc == FZ_OK) rc = fz_selector_set(c, hw, kSelectorParams);
     }
     free(hw);
-    free(perm);
+    free(perm[0]);
+    free(perm[1]);
     free(hl);
     return rc;
 }
@@ -1433,7 +1469,7 @@ int fz_selector_grad(fz_ctx* c, const float* d_feat, const float* d_target, uint
     DeviceGuard dg(c->device);
     hipStream_t st = (hipStream_t)stream;
     TrainBufs tb;
-    if (!tb.alloc_batch((uint32_t)n) || hipMalloc((void**)&tb.loss, sizeof(float)) != hipSuccess) return FZ_ERR_NOMEM;
+    if (!tb.alloc((uint32_t)n, 0, 0)) return FZ_ERR_NOMEM;
     float loss = 0.0f;
     bool ok = hipMemcpyAsync(tb.w, c->sel, sizeof(float) * kSelectorParams, hipMemcpyDeviceToDevice, st) == hipSuccess;
     launch_train_batch(st, tb.w, d_feat, d_target, nullptr, (uint32_t)n, tb.s, tb.loss);

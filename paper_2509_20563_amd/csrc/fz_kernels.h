@@ -45,10 +45,34 @@ void launch_finalize(hipStream_t st, const Geom& g, uint32_t mode, double eb, ui
                      const uint2* pstage, const uint8_t* bpred, const uint64_t* reg_idx, const int32_t* coef,
                      const float* x, uint32_t codec = 0);
 
-// fz_train.hip: selector training (device scratch of one minibatch)
-struct TrainScratch {
-    float *Z, *H1, *H2, *DY, *DH1, *DH2, *SE, *grad;
+// fz_train.hip: selector training.  A minibatch runs on up to kTrainMaxWg
+// workgroups (two per CU), each with a row of partial sums: the gradient and
+// the squared error.
+constexpr int kTrainTile = 16;          // samples a workgroup takes at a time
+constexpr uint32_t kTrainMaxWg = 512;
+constexpr uint32_t kTrainRow = 5504;    // floats of a row, a multiple of 64
+static_assert(kTrainRow > (uint32_t)kSelectorParams, "a row holds the gradient and the squared error");
+constexpr uint32_t kFeatureParts = 256;  // partial sums of the feature statistics
+inline uint32_t train_rows(uint32_t B) {
+    const uint32_t tiles = (B + kTrainTile - 1) / kTrainTile;
+    return tiles < kTrainMaxWg ? tiles : kTrainMaxWg;
+}
+// Adam step of a minibatch (m null: the gradient only)
+struct TrainAdam {
+    float *w, *m, *v;
+    float lr, b1, b2, eps;
+    int t;  // step number, from 1
 };
+// Device scratch of one minibatch: Z = train_rows(B) rows of partial sums.
+// loss_sum (nullable): the minibatch's loss is added to it.
+struct TrainScratch {
+    float *Z, *grad;
+    double* loss_sum;
+    TrainAdam adam;
+};
+// The network's parameters while training: a row, then the scratch of
+// launch_feature_stats.
+constexpr uint64_t kTrainWBytes = sizeof(float) * kTrainRow + sizeof(double) * 2 * kNFeat * kFeatureParts;
 void launch_targets(hipStream_t st, const uint32_t* costs, uint64_t n, float* t);
 void launch_feature_stats(hipStream_t st, const float* feat, uint64_t n, float* w);
 void launch_train_batch(hipStream_t st, const float* w, const float* feat, const float* tgt, const uint32_t* idx,
