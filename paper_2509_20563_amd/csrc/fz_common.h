@@ -540,24 +540,35 @@ __device__ __forceinline__ void block_prefix(int32_t (&v)[8], uint32_t lane) {
         return;
     }
     if (ND == 2) {
-        // x: carry from the (up to 3) lanes before in the same row of 4
-        int32_t tot = v[7], carry = 0;
+        // the whole wave active.  x: carry from the (up to 3) lanes before
+        // in the same row of 4, by DPP row shifts (lanes whose source lies
+        // in another row of 4 masked)
+        const uint32_t lx = lane & 3;
+        uint32_t tot = (uint32_t)v[7];
+        uint32_t o = dpp32<0x111, 0xf>(tot);
+        tot += lx >= 1 ? o : 0u;
+        o = dpp32<0x112, 0xf>(tot);
+        tot += lx >= 2 ? o : 0u;
+        const uint32_t carry = tot - (uint32_t)v[7];
+        // y, lanes 4 apart: inside a row of 16 lanes by DPP row shifts; the
+        // row's column total (two row rotations) then crosses to the later
+        // rows by butterflies over lane ^ 16 and lane ^ 32 (permlane swaps).
 #pragma unroll
-        for (int d = 1; d < 4; d <<= 1) {
-            const int32_t o = __shfl_up(tot, d, 4);
-            if ((lane & 3) >= (uint32_t)d) tot += o;
-        }
-        carry = tot - v[7];
-#pragma unroll
-        for (int i = 0; i < 8; i++) v[i] += carry;
-        // y: lanes 4 apart
-#pragma unroll
-        for (int d = 4; d < 64; d <<= 1) {
-#pragma unroll
-            for (int i = 0; i < 8; i++) {
-                const int32_t o = __shfl_up(v[i], d, 64);
-                if (lane >= (uint32_t)d) v[i] += o;
-            }
+        for (int i = 0; i < 8; i++) {
+            const uint32_t w = (uint32_t)v[i] + carry;
+            uint32_t a = w;
+            a += dpp32<0x114, 0xf>(a);
+            a += dpp32<0x118, 0xf>(a);
+            uint32_t c = w + dpp32<0x128, 0xf>(w);
+            c += dpp32<0x124, 0xf>(c);
+            const auto s16 = __builtin_amdgcn_permlane16_swap(c, c, false, false);
+            uint32_t p = (lane & 16) ? s16[0] : s16[1];  // lane ^ 16
+            a += (lane & 16) ? p : 0u;
+            c += p;
+            const auto s32 = __builtin_amdgcn_permlane32_swap(c, c, false, false);
+            p = (lane & 32) ? s32[0] : s32[1];  // lane ^ 32
+            a += (lane & 32) ? p : 0u;
+            v[i] = (int32_t)a;
         }
         return;
     }

@@ -53,7 +53,8 @@ __device__ __forceinline__ void build_lut(const uint8_t* __restrict__ lensp, uin
     const bool ok = B == 0 && K == (uint32_t)kLut && U >= 2;
     if (!ok) {
         if (t == 0) atomicOr(&misc->flags, F_CORRUPT);
-        for (uint32_t v = t; v < (uint32_t)kLut; v += 1024) lut[v] = 0;
+        // one bit per codeword, so that every decoder still moves on
+        for (uint32_t v = t; v < (uint32_t)kLut; v += 1024) lut[v] = 1;
         return;
     }
     canonical_code(len, cs);
@@ -867,6 +868,19 @@ __global__ __launch_bounds__(256) void k_decode_res(Geom g, const uint32_t* __re
     outlier_totals(t, active, oq, oi0, misc, reinterpret_cast<uint32_t*>(LUT));
 }
 
+// The regression plane floor((A + Bx u + By v + Bz w + 128) / 256), u = 2 lx -
+// (ex - 1) and likewise v, w, added to the residuals of one segment.
+__device__ __forceinline__ void add_plane(int32_t (&v)[8], const int4& c, const BlockInfo& bi, uint32_t lx0,
+                                          uint32_t ly, uint32_t lz) {
+#pragma unroll
+    for (int i = 0; i < 8; i++) {
+        const int64_t sum = (int64_t)c.x + (int64_t)c.y * (2 * (int32_t)(lx0 + i) - ((int32_t)bi.ex - 1)) +
+                            (int64_t)c.z * (2 * (int32_t)ly - ((int32_t)bi.ey - 1)) +
+                            (int64_t)c.w * (2 * (int32_t)lz - ((int32_t)bi.ez - 1)) + 128;
+        v[i] = (int32_t)((uint32_t)v[i] + (uint32_t)(int32_t)(sum >> 8));
+    }
+}
+
 // The blocks the fast decoder leaves as residuals (edge blocks, and
 // second-order blocks, or all blocks of a second-order container): one wave
 // per block, lane = segment of 8 values along x (as the residual layout),
@@ -902,13 +916,7 @@ __global__ __launch_bounds__(256) void k_inverse_wave(Geom g, const int32_t* __r
             int4 c = make_int4(0, 0, 0, 0);
             if (r < nreg) c = reinterpret_cast<const int4*>(coefs)[r];
             else bad = true;
-#pragma unroll
-            for (int i = 0; i < 8; i++) {
-                const int64_t sum = (int64_t)c.x + (int64_t)c.y * (2 * (int32_t)(lx0 + i) - ((int32_t)bi.ex - 1)) +
-                                    (int64_t)c.z * (2 * (int32_t)ly - ((int32_t)bi.ey - 1)) +
-                                    (int64_t)c.w * (2 * (int32_t)lz - ((int32_t)bi.ez - 1)) + 128;
-                v[i] = (int32_t)((uint32_t)v[i] + (uint32_t)(int32_t)(sum >> 8));
-            }
+            add_plane(v, c, bi, lx0, ly, lz);
         }
         uint32_t nvalid;
         const uint64_t row = seg_index<ND>(g, bi, lane, nvalid);
@@ -929,6 +937,315 @@ __global__ __launch_bounds__(256) void k_inverse_wave(Geom g, const int32_t* __r
     }
     if (__ballot(bad) && lane == 0) atomicOr(&misc->flags, F_CORRUPT);
 }
+
+// ------------------------------------------------- one wave per block decode
+// Few blocks (a small field, or the truncated blocks at the edges of a
+// large one): with a lane per block the kernel lasts as long as one lane's
+// chain of 512 codewords, 45-85 us however few blocks there are.  Here a
+// wave shares a block's bits: lane i walks the codewords that start in the
+// i-th of 64 equal parts of the bit string, first from the part's first
+// bit (a guess, exact for lane 0), then again from where lane i - 1 ended,
+// until no lane's start changes.  A Huffman code falls into step with
+// itself after a few codewords, so 2 to 8 rounds settle nearly every block
+// (28 to 83 codewords one after the other in place of 512, host simulation
+// over Gaussian random fields, waves, noise and positions at 1 to 9.6 bits
+// a value); a round settles at least one more lane whatever the code, so
+// at most 64 are needed.  A scan of the lanes' codeword counts then gives
+// each lane its place, a last pass leaves the residuals in LDS, and lane =
+// segment of 8 values applies the inverse in registers (as k_unshuffle).
+//
+// It issues about five times the instructions of the lane decoder per
+// block (1250 per wave and 2D block, 62% of the time of 8000 blocks), hence
+// the rule of launch_wave's callers (kWaveBlocks).  A 1800 x 3600 field
+// (12769 blocks, 449 at the edges): 48 us, where the lane decoders took 48
+// for the interior and 53 after it for the edges.
+constexpr int kWaveWords = 200;  // 31 + 6144 bits, the codeword across the end, two words of window
+constexpr int kWaveField = 0, kWaveRow = 1, kWavePred = 2;
+
+// The e-th block that is not interior: planes of blocks past ib2, then rows
+// past ib1, then columns past ib0 (at most one of each).
+__device__ __forceinline__ uint32_t edge_block(const Geom& g, const uint32_t ib[3], uint32_t e) {
+    const uint32_t nz = g.nb[0] * g.nb[1] * (g.nb[2] - ib[2]);
+    if (e < nz) return g.nb[0] * g.nb[1] * ib[2] + e;
+    e -= nz;
+    const uint32_t ny = g.nb[0] * (g.nb[1] - ib[1]) * ib[2];
+    if (e < ny) {
+        const uint32_t row = g.nb[0] * (g.nb[1] - ib[1]);
+        const uint32_t z = e / row;
+        return g.nb[0] * (ib[1] + g.nb[1] * z) + (e - z * row);
+    }
+    e -= ny;
+    const uint32_t nx = g.nb[0] - ib[0];
+    const uint32_t r = e / nx, z = r / ib[1];
+    return ib[0] + (e - r * nx) + g.nb[0] * ((r - z * ib[1]) + g.nb[1] * z);
+}
+
+// kWaveField: first-order Lorenzo, dequantised rows to out; kWaveRow:
+// residuals, row-major int32, to out; kWavePred: the block's own predictor
+// (fixed_pred >= 0, or bpred), dequantised rows to out.  edges: the blocks
+// past ib only.
+template <int ND, int MODE>
+__global__ __launch_bounds__(256) void k_decode_wave(
+    Geom g, uint32_t count, int edges, uint32_t ib0, uint32_t ib1, uint32_t ib2, const uint32_t* __restrict__ stream,
+    uint64_t nwords, const uint64_t* __restrict__ off, const uint16_t* __restrict__ chunks,
+    const uint16_t* __restrict__ lut_g, const uint32_t* __restrict__ opos, const int32_t* __restrict__ oval,
+    const uint2* __restrict__ oidx, uint64_t n_out, double e2, float* __restrict__ out, int vec, Misc* misc,
+    int fixed_pred, const uint8_t* __restrict__ bpred, const uint64_t* __restrict__ reg_idx,
+    const int32_t* __restrict__ coefs, uint64_t nreg) {
+    __shared__ __align__(16) uint16_t LUT[kLut];
+    __shared__ uint32_t WORDS[4][kWaveWords];
+    __shared__ __align__(16) int16_t SYM[4][kBlockElems + 64];
+    const uint32_t t = threadIdx.x, lane = t & 63;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(t >> 6));
+    uint32_t* W = WORDS[wave];
+    int16_t* R = SYM[wave];
+    const uint32_t ib[3] = {ib0, ib1, ib2};
+    bool bad = false;
+    uint32_t c_out = 0;
+    uint64_t h_out = 0;
+    // what locates a block's bits and outliers is loaded one block ahead
+    // (the first one's with the table), as each of these loads is a memory
+    // latency the decode would otherwise wait for
+    const uint32_t e0 = blockIdx.x * 4 + wave, estep = gridDim.x * 4;
+    uint32_t nb_ = 0, nT = 0;
+    uint64_t nstart = 0;
+    uint2 nspan = make_uint2(0, 0);
+    auto locate = [&](uint32_t e) {
+        if (e >= count) return;
+        nb_ = edges ? edge_block(g, ib, e) : e;
+        nstart = off[nb_];
+        nT = chunks[nb_];
+        if (n_out) nspan = oidx[nb_];
+    };
+    locate(e0);
+    {
+        const uint32_t* src = reinterpret_cast<const uint32_t*>(lut_g);
+        uint32_t* dst = reinterpret_cast<uint32_t*>(LUT);
+#pragma unroll
+        for (int k = 0; k < kLut / 2 / 256; k++) dst[t + 256 * k] = src[t + 256 * k];
+    }
+    __syncthreads();
+    for (uint32_t e = e0; e < count; e += estep) {
+        const uint32_t b = nb_;
+        const BlockInfo bi = block_info(g, b);
+        const uint64_t start = nstart;
+        const uint2 span = nspan;
+        uint32_t T = nT;
+        const uint32_t nv_blk = bi.ex * bi.ey * bi.ez;
+        if (T > (uint32_t)(kBlockElems * kLmax)) {  // no block has more
+            bad = true;
+            T = kBlockElems * kLmax;
+        }
+        const uint64_t w0 = start >> 5;
+        const uint32_t s0 = (uint32_t)(start & 31);
+        const uint32_t nw = (s0 + T + 31) / 32 + 3;
+        // the block's first 64 outliers
+        uint32_t fpos = 0;
+        int32_t fval = 0;
+        {
+            const uint64_t k = (uint64_t)span.x + lane;
+            if (k < span.y && k < n_out) {
+                fpos = opos[k];
+                fval = oval[k];
+            }
+        }
+        {
+            // at most four words per lane, every load issued before the
+            // first is stored
+            uint32_t v[4];
+#pragma unroll
+            for (uint32_t k = 0; k < 4; k++) {
+                v[k] = 0;
+                if (64 * k < nw && w0 + 64 * k + lane < nwords) v[k] = stream[w0 + 64 * k + lane];
+            }
+#pragma unroll
+            for (uint32_t k = 0; k < 4; k++)
+                if (64 * k + lane < kWaveWords) W[64 * k + lane] = v[k];
+        }
+        locate(e + estep);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        // up to four codewords from the 64 bits at bit p
+        auto window = [&](uint32_t p) -> uint64_t {
+            const uint32_t k = p >> 5, s = p & 31;
+            const uint64_t hi = (((uint64_t)W[k] << 32) | W[k + 1]) << s;
+            return hi | (((uint64_t)W[k + 2] << s) >> 32);
+        };
+        // positions count from the first word's first bit
+        const uint32_t S = (T + 63) / 64, end = s0 + T;
+        const uint32_t pend = min(s0 + (lane + 1) * S, end);
+        uint32_t pst = min(s0 + lane * S, end), pe = 0, n = 0;
+        bool todo = true;
+        while (__ballot(todo)) {
+            uint32_t p = todo ? pst : pend;
+            uint32_t c = 0;
+            while (__ballot(p < pend)) {
+                uint64_t buf = window(min(p, end));
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    // looked up by every lane (no branch per codeword)
+                    const bool act = p < pend;
+                    const uint32_t en = LUT[(uint32_t)(buf >> (64 - kLmax))];
+                    const uint32_t len = act ? en & 63u : 0u;
+                    buf <<= len;
+                    p += len;
+                    c += act ? 1u : 0u;
+                }
+            }
+            if (todo) {
+                pe = p;
+                n = c;
+            }
+            const uint32_t prev = (uint32_t)__shfl_up((int)pe, 1, 64);
+            todo = lane > 0 && prev != pst;
+            if (todo) pst = prev;
+        }
+        // a walk that starts past its part's end holds no codeword
+        const uint32_t incl = wave_incl_scan(n);
+        bad |= lane == 63 && (incl != nv_blk || pe != end);
+        uint32_t at = incl - n;
+        {
+            // a lane that is through writes past the block's slots
+            uint32_t p = pst;
+            const uint32_t to = at + n;
+            while (__ballot(at < to)) {
+                uint64_t buf = window(min(p, end));
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    const bool act = at < to;
+                    const uint32_t en = LUT[(uint32_t)(buf >> (64 - kLmax))];
+                    R[act && at < (uint32_t)kBlockElems ? at : kBlockElems + lane] = (int16_t)entry_residual(en);
+                    const uint32_t len = act ? en & 63u : 0u;
+                    buf <<= len;
+                    p += len;
+                    at += act ? 1u : 0u;
+                }
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        // lane = segment of 8 values
+        uint32_t nvalid;
+        const uint64_t row = seg_index<ND>(g, bi, lane, nvalid);
+        uint32_t lx0, ly, lz;
+        seg_coords<ND>(lane, lx0, ly, lz);
+        int32_t d[8];
+        if (nv_blk == (uint32_t)kBlockElems) {  // uniform
+            const int4 r = *reinterpret_cast<const int4*>(&R[8 * lane]);
+            const int32_t v[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                d[2 * i] = (int32_t)((uint32_t)v[i] << 16) >> 16;
+                d[2 * i + 1] = v[i] >> 16;
+            }
+        } else {
+            const uint32_t r0 = (lz * bi.ey + ly) * bi.ex + lx0;
+#pragma unroll
+            for (int i = 0; i < 8; i++) d[i] = (uint32_t)i < nvalid ? (int32_t)R[r0 + i] : 0;
+        }
+        __builtin_amdgcn_wave_barrier();
+        uint32_t om = 0;
+#pragma unroll
+        for (int i = 0; i < 8; i++) om |= (d[i] == -kRadius ? 1u : 0u) << i;
+        if (__ballot(om != 0)) {
+            // the block's outliers in slot order: rank = earlier lanes' and
+            // earlier ones of this lane
+            const uint32_t nol = (uint32_t)__popc(om);
+            const uint32_t oincl = wave_incl_scan(nol);
+            const uint32_t oincl_max = (uint32_t)__builtin_amdgcn_readlane((int)oincl, 63);
+            bad |= span.y - span.x != oincl_max;
+            const uint32_t r = span.x + oincl - nol;
+            const uint32_t pos0 = b * kBlockElems + 8 * lane;
+            if (oincl_max <= 64) {  // uniform: all of them sit in the lanes
+#pragma unroll
+                for (int i = 0; i < 8; i++) {
+                    const uint32_t k = oincl - nol + (uint32_t)__popc(om & ((1u << i) - 1u));
+                    const uint32_t op = (uint32_t)__shfl((int)fpos, (int)k, 64);
+                    const int32_t ov = __shfl(fval, (int)k, 64);
+                    const bool is = (om >> i) & 1u;
+                    const bool ok = op == pos0 + i && (uint64_t)span.x + k < n_out;
+                    bad |= is && !ok;
+                    d[i] = is ? (ok ? ov : 0) : d[i];
+                }
+            } else {
+                // every load issued at once (a value that is no outlier
+                // reads the entry its lane's next outlier would take)
+                uint32_t op[8];
+                int32_t ov[8];
+#pragma unroll
+                for (int i = 0; i < 8; i++) {
+                    const uint64_t k = (uint64_t)r + (uint32_t)__popc(om & ((1u << i) - 1u));
+                    const uint64_t kc = n_out ? (k < n_out ? k : n_out - 1) : 0;
+                    op[i] = n_out ? opos[kc] : 0u;
+                    ov[i] = n_out ? oval[kc] : 0;
+                }
+#pragma unroll
+                for (int i = 0; i < 8; i++) {
+                    const uint64_t k = (uint64_t)r + (uint32_t)__popc(om & ((1u << i) - 1u));
+                    const bool is = (om >> i) & 1u;
+                    const bool ok = k < span.y && k < n_out && op[i] == pos0 + i;
+                    bad |= is && !ok;
+                    d[i] = is ? (ok ? ov[i] : 0) : d[i];
+                }
+            }
+            c_out += nol;
+            h_out += pos_hash(pos0 >> 3) * (uint64_t)om;
+        } else {
+            bad |= span.x != span.y;
+        }
+        if (MODE == kWaveRow) {
+            int32_t* res = reinterpret_cast<int32_t*>(out);
+            if (nvalid == 8 && vec && (row & 3) == 0) {
+                int4* o4 = reinterpret_cast<int4*>(res + row);
+                o4[0] = make_int4(d[0], d[1], d[2], d[3]);
+                o4[1] = make_int4(d[4], d[5], d[6], d[7]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 8; i++)
+                    if ((uint32_t)i < nvalid) res[row + i] = d[i];
+            }
+            continue;
+        }
+        const uint32_t pr = MODE == kWavePred ? (fixed_pred >= 0 ? (uint32_t)fixed_pred : bpred[b]) : 0u;
+        if (pr <= 1) {
+            block_prefix<ND>(d, lane);
+            if (pr == 1) block_prefix<ND>(d, lane);
+        } else {
+            const uint64_t r = fixed_pred >= 0 ? b : reg_idx[b];
+            int4 cf = make_int4(0, 0, 0, 0);
+            if (r < nreg) cf = reinterpret_cast<const int4*>(coefs)[r];
+            else bad = true;
+            add_plane(d, cf, bi, lx0, ly, lz);
+        }
+        if (nvalid) {
+            float f[8];
+#pragma unroll
+            for (int i = 0; i < 8; i++) f[i] = (float)((double)d[i] * e2);
+            if (nvalid == 8 && vec && (row & 3) == 0) {
+                f32x4* o4 = reinterpret_cast<f32x4*>(out + row);
+                o4[0] = f32x4{f[0], f[1], f[2], f[3]};
+                o4[1] = f32x4{f[4], f[5], f[6], f[7]};
+            } else {
+#pragma unroll
+                for (int i = 0; i < 8; i++)
+                    if ((uint32_t)i < nvalid) out[row + i] = f[i];
+            }
+        }
+    }
+    if (__ballot(bad) && lane == 0) atomicOr(&misc->flags, F_CORRUPT);
+    OutQ oq;
+    oq.oi = c_out;
+    oq.hash = h_out;
+    outlier_totals(t, true, oq, 0, misc, reinterpret_cast<uint32_t*>(LUT));
+}
+
+// Blocks a wave-per-block launch takes at most.  Measured, decode of a 3D
+// field alone (us, lane per block / wave per block): at 1e-2 512 blocks 46 /
+// 12, 4096 47 / 17, 13824 47 / 34, 21952 47 / 47; at 2e-4, with blocks of
+// outliers, 82 / 32, 81 / 30, 80 / 64, 80 / 84.
+constexpr uint32_t kWaveBlocks = 16384;
 
 // ------------------------------------------------------ outlier block index
 // Per block, the list index of its first outlier (oidx[b].x) and one past
@@ -1072,6 +1389,28 @@ Interior interior_of(const Geom& g) {
     return r;
 }
 
+// Wave-per-block decode of all blocks (edges false) or of those outside
+// the interior.
+template <int MODE>
+void launch_wave(hipStream_t st, const Geom& g, const Interior& I, bool edges, const uint32_t* stream,
+                 uint64_t stream_words, const uint64_t* off, const uint16_t* chunks, const uint16_t* lut,
+                 const uint32_t* opos, const int32_t* oval, const uint2* oidx, uint64_t n_out, double e2, float* out,
+                 int vec, Misc* misc, int fixed_pred = 0, const uint8_t* bpred = nullptr,
+                 const uint64_t* reg_idx = nullptr, const int32_t* coefs = nullptr, uint64_t nreg = 0) {
+    const uint32_t count = edges ? g.nblocks - I.n : g.nblocks;
+    if (!count) return;
+    // at most what runs together (8 waves per SIMD)
+    const dim3 grid(count < 8192 ? (count + 3) / 4 : 2048);
+#define FZ_WAVE(NDV)                                                                                              \
+    hipLaunchKernelGGL((k_decode_wave<NDV, MODE>), grid, dim3(256), 0, st, g, count, edges ? 1 : 0, I.ib[0],       \
+                       I.ib[1], I.ib[2], stream, stream_words, off, chunks, lut, opos, oval, oidx, n_out, e2, out, \
+                       vec, misc, fixed_pred, bpred, reg_idx, coefs, nreg)
+    if (g.ndim == 3) FZ_WAVE(3);
+    else if (g.ndim == 2) FZ_WAVE(2);
+    else FZ_WAVE(1);
+#undef FZ_WAVE
+}
+
 }  // namespace
 
 // Outlier list index and list hash (before either decoder).
@@ -1079,8 +1418,13 @@ void launch_outlier_index(hipStream_t st, const Geom& g, const uint32_t* opos, u
                           Misc* misc) {
     // ofirst and oend were cleared by the call's reset kernel
     if (!n_out) return;
-    // about 16 groups of 4 entries per thread, at most 1024 workgroups
-    uint64_t og = (n_out + 4 * 16 * 256 - 1) / (4 * 16 * 256);
+    // one group of 4 entries per thread up to 128 workgroups (a thread's
+    // groups are one memory latency each: 12769 entries took 20 us in one
+    // workgroup, 4 us in 13), then up to 16 groups per thread, as every
+    // workgroup adds two atomics on one address (12 ns each), and at most
+    // 1024 workgroups
+    const uint64_t og1 = (n_out + 4 * 256 - 1) / (4 * 256), og16 = (og1 + 15) / 16;
+    uint64_t og = og1 < 128 ? og1 : (og16 > 128 ? og16 : 128);
     if (og > 1024) og = 1024;
     const int vec = ((uintptr_t)opos & 15) == 0;
     hipLaunchKernelGGL(k_outlier_index, dim3((uint32_t)og), dim3(256), 0, st, opos, n_out, g.nblocks, oidx,
@@ -1092,6 +1436,11 @@ void launch_decode(hipStream_t st, const Geom& g, const uint32_t* stream, uint64
                    const int32_t* oval, const uint2* oidx, uint64_t n_out, double e2, float* out,
                    int vec, Misc* misc) {
     const Interior I = interior_of(g);
+    if (g.nblocks <= kWaveBlocks) {
+        launch_wave<kWaveField>(st, g, I, false, stream, stream_words, off, chunks, lut, opos, oval, oidx, n_out, e2,
+                                out, vec, misc);
+        return;
+    }
     const bool fast = I.n > 0;
     if (fast) {
         const uint32_t fg = (I.n + 255) / 256;
@@ -1120,6 +1469,11 @@ void launch_decode(hipStream_t st, const Geom& g, const uint32_t* stream, uint64
 #undef FZ_FAST
     }
     if (fast && I.n == g.nblocks) return;
+    if (g.nblocks - I.n <= kWaveBlocks) {
+        launch_wave<kWaveField>(st, g, I, true, stream, stream_words, off, chunks, lut, opos, oval, oidx, n_out, e2,
+                                out, vec, misc);
+        return;
+    }
     const uint32_t grid = (g.nblocks + 255) / 256;
     const int skip = fast ? 1 : 0;
 #define FZ_GEN(NDV)                                                                                                 \
@@ -1141,6 +1495,11 @@ void launch_decode_pred(hipStream_t st, const Geom& g, const uint32_t* stream, u
                         int fixed_pred, const uint8_t* bpred, const uint64_t* reg_idx, const int32_t* coefs,
                         uint64_t nreg, double e2, float* out, int vec, Misc* misc) {
     const Interior I = interior_of(g);
+    if (g.nblocks <= kWaveBlocks) {
+        launch_wave<kWavePred>(st, g, I, false, stream, stream_words, off, chunks, lut, opos, oval, oidx, n_out, e2,
+                               out, vec, misc, fixed_pred, bpred, reg_idx, coefs, nreg);
+        return;
+    }
     // interior blocks: the fast decoder finishes first-order and regression
     // blocks (a second-order container only gets its residuals there)
     const bool fused = I.n && fixed_pred != 1;
@@ -1194,6 +1553,11 @@ void launch_decode_residuals(hipStream_t st, const Geom& g, const uint32_t* stre
     // stores where a wave covers one run of 64 blocks along x)
     const Interior I = interior_of(g);
     float* rf = reinterpret_cast<float*>(res);
+    if (g.nblocks <= kWaveBlocks) {
+        launch_wave<kWaveRow>(st, g, I, false, stream, stream_words, off, chunks, lut, opos, oval, oidx, n_out, 0.0,
+                              rf, vec, misc);
+        return;
+    }
     if (I.n) {
         const uint32_t fg = (I.n + 255) / 256;
 #define FZ_ARGS                                                                                                     \
@@ -1214,6 +1578,11 @@ void launch_decode_residuals(hipStream_t st, const Geom& g, const uint32_t* stre
 #undef FZ_ARGS
     }
     if (I.n == g.nblocks) return;
+    if (g.nblocks - I.n <= kWaveBlocks) {
+        launch_wave<kWaveRow>(st, g, I, true, stream, stream_words, off, chunks, lut, opos, oval, oidx, n_out, 0.0,
+                              rf, vec, misc);
+        return;
+    }
     const uint32_t grid = (g.nblocks + 255) / 256;
     const int skip = I.n ? 1 : 0;
 #define FZ_DRES(NDV)                                                                                              \
