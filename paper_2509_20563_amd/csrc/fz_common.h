@@ -483,26 +483,39 @@ struct CanonShared {
 
 __device__ inline uint32_t canonical_code(uint32_t len, CanonShared& sh) {
     const uint32_t t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    uint32_t myrank = 0;
-    for (int L = 1; L <= kLmax; L++) {
-        uint64_t m = __ballot(len == (uint32_t)L);
-        if (lane == 0) sh.wave_cnt[L][wave] = __popcll(m);
-        if (len == (uint32_t)L) myrank = __popcll(m & ((1ull << lane) - 1));
+    // lanes of the wave with the same length, from one ballot per bit of it
+    uint64_t same = ~0ull;
+#pragma unroll
+    for (int b = 0; b < 4; b++) {
+        const bool bit = (len >> b) & 1u;
+        const uint64_t m = __ballot(bit);
+        same &= bit ? m : ~m;
     }
+    const uint32_t myrank = (uint32_t)__popcll(same & ((1ull << lane) - 1));
+    if (lane >= 1 && lane <= (uint32_t)kLmax) sh.wave_cnt[lane][wave] = 0;
+    __builtin_amdgcn_wave_barrier();
+    if (len > 0 && len <= (uint32_t)kLmax && myrank == 0) sh.wave_cnt[len][wave] = (uint32_t)__popcll(same);
     __syncthreads();
     if (wave == 0) {
         // lane L (1..kLmax): exclusive prefix of its length's counts over
-        // the waves; then first code and sorted offset per length, in order
+        // the waves (every count loaded before the first is replaced); then
+        // first code and sorted offset per length, in order, the counts
+        // read across lanes as scalars
         uint32_t c = 0;
-        if (lane >= 1 && lane <= (uint32_t)kLmax)
+        if (lane >= 1 && lane <= (uint32_t)kLmax) {
+            uint32_t v[16];
+#pragma unroll
+            for (int w = 0; w < 16; w++) v[w] = sh.wave_cnt[lane][w];
+#pragma unroll
             for (int w = 0; w < 16; w++) {
-                const uint32_t v = sh.wave_cnt[lane][w];
                 sh.wave_cnt[lane][w] = c;
-                c += v;
+                c += v[w];
             }
+        }
         uint32_t code = 0, off = 0;
+#pragma unroll
         for (int L = 1; L <= kLmax; L++) {
-            const uint32_t cL = (uint32_t)__shfl((int)c, L, 64);
+            const uint32_t cL = (uint32_t)__builtin_amdgcn_readlane((int)c, L);
             if (lane == (uint32_t)L) {
                 sh.count[L] = cL;
                 sh.first[L] = code;

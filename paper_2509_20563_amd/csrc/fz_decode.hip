@@ -58,19 +58,19 @@ __device__ __forceinline__ void build_lut(const uint8_t* __restrict__ lensp, uin
         return;
     }
     canonical_code(len, cs);
-    for (uint32_t v = t; v < (uint32_t)kLut; v += 1024) {
-        uint16_t e = 0;
-        for (int L = 1; L <= kLmax; L++) {
-            const uint32_t c = cs.count[L];
-            if (!c) continue;
-            const uint32_t end = (cs.first[L] + c) << (kLmax - L);
-            if (v < end) {
-                const uint32_t idx = (v >> (kLmax - L)) - cs.first[L];
-                e = (uint16_t)(((cs.sorted[cs.offset[L] + idx] ^ (uint32_t)kRadius) << 6) | (uint32_t)L);
-                break;
-            }
-        }
-        lut[v] = e;
+    // first prefix past each length's codewords (non-decreasing): a prefix's
+    // length is one more than the lengths it lies past
+    uint32_t end[kLmax];
+#pragma unroll
+    for (int L = 1; L < kLmax; L++) end[L] = (cs.first[L] + cs.count[L]) << (kLmax - L);
+#pragma unroll
+    for (uint32_t k = 0; k < (uint32_t)kLut / 1024; k++) {
+        const uint32_t v = t + 1024 * k;
+        uint32_t L = 1;
+#pragma unroll
+        for (int l = 1; l < kLmax; l++) L += v >= end[l] ? 1u : 0u;
+        const uint32_t idx = (v >> (kLmax - L)) - cs.first[L];
+        lut[v] = (uint16_t)(((cs.sorted[cs.offset[L] + idx] ^ (uint32_t)kRadius) << 6) | L);
     }
 }
 

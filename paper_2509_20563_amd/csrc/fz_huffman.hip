@@ -20,31 +20,209 @@ namespace fz {
 // the first 2n-2 items of list[1], each selected package standing for the
 // next two items one level deeper.  A symbol's length is the number of
 // levels at which it is selected.  Leaves keep their sorted order in every
-// list, so a level is summarised by a bitmask of leaf positions.
+// list, so a level is summarised by the leaves' positions in it.
+//
+// One workgroup, bound by the latency of its serial steps and, at many used
+// symbols, by the instructions its 16 waves issue, so the work follows the
+// number of used symbols n: these are compacted first, and the sort runs
+// over the next power of two.  A list is never stored: the lane that merges
+// items 2i and 2i + 1 of list l adds them to package i of list l - 1, one
+// barrier per level.  W is the type of the weights: a package weighs at
+// most kLmax times the field's values, 32 bits up to 2^32 / kLmax values.
+// Measured: 20 / 100 / 300 / 1000 used symbols 16.0 / 19.2 / 24.0 / 30.7 us
+// with the launch, against 22.7 / 26 / 33 / 41 us with two full binary
+// searches per level over stored lists (a step is about 250 cycles of LDS
+// latency and dependent instructions, a level three barriers and reads on
+// top) and LDS permutes in the sort.
+struct PackageShared {
+    uint16_t pos[kLmax][kBins + 2];  // [l]: position of leaf t in list l (1..kLmax-1); [kBins]: unused writes
+    uint32_t take[kLmax + 1];
+};
+
+// Code length of leaf t (0 past the n leaves): thread t holds the weight of
+// leaf t; leaf, p0 and p1 are LDS arrays of kBins.
+template <class W>
+__device__ uint32_t package_merge(W w, uint32_t n, W* leaf, W* p0, W* p1, PackageShared& sh) {
+    const uint32_t t = threadIdx.x, lane = t & 63;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(t >> 6));
+    const bool is_leaf = t < n;
+    if (is_leaf) leaf[t] = w;
+    __syncthreads();
+    W* cur = p0;
+    W* nxt = p1;
+    uint32_t np = n / 2;
+    if (t < np) cur[t] = leaf[2 * t] + leaf[2 * t + 1];
+    __syncthreads();
+    // leaves among the first 2 t items of the previous level's list.  Going
+    // up a level a list only gains items, its packages only get lighter,
+    // and this count only falls, by about half as much per level (1000
+    // codes: at most 118, 49, 21, 9, 4, ... places), so the search starts
+    // there and gallops down.
+    // No branch inside the search: a step is the LDS latency and about ten
+    // instructions, and every taken branch would add to it.
+    constexpr uint32_t kHalve = 1u << 16;  // gallop step that halves the range
+    const uint32_t d = 2 * t;
+    uint32_t hint = n;
+#pragma unroll 1
+    for (int l = kLmax - 1; l >= 1; l--) {
+        const uint32_t len = n + np;
+        if (128 * wave < len) {
+            uint32_t lo = d > np ? d - np : 0u, hi = min(hint, min(d, n)), g = hint == n ? kHalve : 1u;
+            lo = d < len ? lo : hi;
+            while (__ballot(lo < hi)) {
+                // leaf m comes before package d - 1 - m
+                const uint32_t m = hi - min(g, (hi - lo + 1) >> 1);
+                const W a = leaf[min(m, (uint32_t)kBins - 1)], c = cur[min(d - 1 - m, (uint32_t)kBins - 1)];
+                const bool before = a <= c, in = lo < hi;
+                lo = in && before ? m + 1 : lo;
+                hi = in && !before ? m : hi;
+                g = before ? kHalve : min(2 * g, kHalve);
+            }
+            // the lane's items 2 t and 2 t + 1: leaf i or package j, the next
+            const uint32_t i = lo, j = d - lo;
+            hint = d < len ? i : n;
+            const bool i0 = i < n, i1 = i + 1 < n, j0 = j < np, j1 = j + 1 < np;
+            const W a0 = leaf[min(i, (uint32_t)kBins - 1)], a1 = leaf[min(i + 1, (uint32_t)kBins - 1)],
+                    b0 = cur[min(j, (uint32_t)kBins - 1)], b1 = cur[min(j + 1, (uint32_t)kBins - 1)];
+            const bool f0 = i0 & (!j0 | (a0 <= b0));                                   // the first is a leaf
+            const bool f1 = f0 ? i1 & (!j0 | (a1 <= b0)) : i0 & (!j1 | (a0 <= b1));   // the second is
+            sh.pos[l][f0 && d < len ? i : (uint32_t)kBins] = (uint16_t)d;
+            sh.pos[l][f1 && d + 1 < len ? i + (f0 ? 1u : 0u) : (uint32_t)kBins] = (uint16_t)(d + 1);
+            const W sum = (f0 ? a0 : b0) + (f1 ? (f0 ? a1 : a0) : (f0 ? b0 : b1));
+            nxt[t] = sum;
+        }
+        __syncthreads();
+        W* tmp = cur;
+        cur = nxt;
+        nxt = tmp;
+        np = len / 2;
+    }
+    if (wave == 0) {
+        // leaves among the first `take` items of each level, their positions
+        // ascending: every step-th leaf, then those after the last of these
+        const uint32_t step = (n + 63) / 64;
+        uint32_t take = 2 * n - 2;
+        uint32_t c[kLmax];
+#pragma unroll
+        for (int l = 1; l < kLmax; l++) c[l] = step * lane < n ? sh.pos[l][step * lane] : 0xFFFFu;
+#pragma unroll
+        for (int l = 1; l < kLmax; l++) {
+            uint32_t k = (uint32_t)__popcll(__ballot(c[l] < take));
+            if (step > 1 && k) {
+                const uint32_t j = step * (k - 1) + lane;
+                const uint32_t p = sh.pos[l][j < n ? j : 0];
+                k = step * (k - 1) + (uint32_t)__popcll(__ballot(lane < step && j < n && p < take));
+            }
+            if (lane == 0) sh.take[l] = take;
+            take = 2 * (take - k);
+        }
+        if (lane == 0) sh.take[kLmax] = take;
+    }
+    __syncthreads();
+    uint32_t L = 0;
+    if (is_leaf) {
+#pragma unroll
+        for (int l = 1; l < kLmax; l++) L += sh.pos[l][t] < sh.take[l] ? 1u : 0u;
+        L += t < sh.take[kLmax] ? 1u : 0u;
+    }
+    return L;
+}
+
+// Bitonic stages inside a wave.  Both values of a pair are at hand in each of
+// its lanes; `max_lanes` are the lanes that keep the larger one, and the
+// comparison's ballot, flipped there, selects.
+__device__ __forceinline__ uint64_t pick64(uint64_t lanes, uint64_t set, uint64_t clear) {
+    return __builtin_amdgcn_inverse_ballot_w64(lanes) ? set : clear;
+}
+template <int J>
+__device__ __forceinline__ uint64_t bitonic_stage(uint64_t v, uint64_t max_lanes) {
+    const uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
+    if (J >= 16) {
+        // the swaps leave the pair's values in order in both lanes
+        uint64_t a, b;
+        if (J == 16) {
+            const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+            const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+            a = (uint64_t)h[0] << 32 | l[0];
+            b = (uint64_t)h[1] << 32 | l[1];
+        } else {
+            const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+            const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+            a = (uint64_t)h[0] << 32 | l[0];
+            b = (uint64_t)h[1] << 32 | l[1];
+        }
+        return pick64(__ballot(b < a) ^ max_lanes, b, a);
+    }
+    // lane ^ 1, 2: quad permutes; ^ 4: mirror of 8 lanes, then of each quad;
+    // ^ 8: rotation of the row of 16
+    constexpr int kCtrl = J == 1 ? 0xB1 : (J == 2 ? 0x4E : (J == 4 ? 0x141 : 0x128));
+    uint32_t ol = dpp32<kCtrl, 0xf>(lo), oh = dpp32<kCtrl, 0xf>(hi);
+    if (J == 4) {
+        ol = dpp32<0x1B, 0xf>(ol);
+        oh = dpp32<0x1B, 0xf>(oh);
+    }
+    const uint64_t o = (uint64_t)oh << 32 | ol;
+    return pick64(__ballot(o < v) ^ max_lanes, o, v);
+}
+// Lanes with bit J set.
+template <int J>
+constexpr uint64_t lanes_with() {
+    uint64_t m = 0;
+    for (int l = 0; l < 64; l++) m |= (uint64_t)((l & J) != 0) << l;
+    return m;
+}
+// Stage J of the merge of size K < 64 (directions alternate inside the wave)
+template <int K, int J>
+__device__ __forceinline__ uint64_t stage_in(uint64_t v) {
+    return bitonic_stage<J>(v, lanes_with<J>() ^ lanes_with<K>());
+}
+// The last six stages of a merge of 64 or more, `down`: descending.
+__device__ __forceinline__ uint64_t merge_wave(uint64_t v, bool down) {
+    const uint64_t f = down ? ~0ull : 0ull;
+    v = bitonic_stage<32>(v, lanes_with<32>() ^ f);
+    v = bitonic_stage<16>(v, lanes_with<16>() ^ f);
+    v = bitonic_stage<8>(v, lanes_with<8>() ^ f);
+    v = bitonic_stage<4>(v, lanes_with<4>() ^ f);
+    v = bitonic_stage<2>(v, lanes_with<2>() ^ f);
+    return bitonic_stage<1>(v, lanes_with<1>() ^ f);
+}
+
 __global__ __launch_bounds__(1024) void k_codebook(uint32_t* __restrict__ hist, uint8_t* __restrict__ out_lens,
                                                    uint32_t* __restrict__ cw, Misc* misc) {
-    __shared__ uint64_t key[kBins];
-    __shared__ uint64_t la[2 * kBins], lb[2 * kBins];
-    __shared__ uint32_t mask[kLmax + 1][64];
-    __shared__ uint32_t klev[kLmax + 2];
+    // the sort's two buffers, then (the sort done) the arrays of package_merge
+    __shared__ uint64_t buf[3][kBins];
+    __shared__ PackageShared ps;
     __shared__ uint8_t slen[kBins];
-    __shared__ uint32_t s_first_unused;
+    __shared__ uint32_t s_first_unused, s_used[16];
     __shared__ uint64_t red[16];
     __shared__ CanonShared cs;
 
-    const uint32_t t = threadIdx.x;
+    const uint32_t t = threadIdx.x, lane = t & 63;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(t >> 6));
+    auto add = [](uint64_t a, uint64_t b) { return a + b; };
     // sum the histogram copies; copy 0 keeps the total, the others are
-    // cleared
+    // cleared (at the end: a barrier waits for stores)
     uint32_t h = 0;
 #pragma unroll
     for (int k = 0; k < kHistCopies; k++) h += hist[k * kBins + t];
-    hist[t] = h;
-#pragma unroll
-    for (int k = 1; k < kHistCopies; k++) hist[k * kBins + t] = 0;
     slen[t] = 0;
-    key[t] = h ? (((uint64_t)h << 10) | t) : ~0ull;
     if (t == 0) s_first_unused = kBins;
-    const int n = __syncthreads_count(h > 0);
+    const uint64_t um = __ballot(h > 0);
+    const uint64_t wtotal = wave_incl_scan64(h, add);
+    if (lane == 63) {
+        s_used[wave] = (uint32_t)__popcll(um);
+        red[wave] = wtotal;
+    }
+    __syncthreads();
+    uint32_t n = 0, before = 0;
+    uint64_t total = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < 16; w++) {
+        const uint32_t v = s_used[w];
+        before += w < wave ? v : 0u;
+        n += v;
+        total += red[w];
+    }
 
     if (n == 1) {
         if (h == 0) atomicMin(&s_first_unused, t);
@@ -52,108 +230,77 @@ __global__ __launch_bounds__(1024) void k_codebook(uint32_t* __restrict__ hist, 
         if (h > 0) slen[t] = 1;
         if (t == s_first_unused) slen[t] = 1;
     } else if (n >= 2) {
-        // bitonic sort of (count << 10 | symbol), unused symbols last; a
-        // thread keeps its key in a register: partners closer than 64 are
-        // exchanged inside the wave, farther ones through two alternating
-        // LDS buffers (one barrier per such stage)
-        uint64_t v = key[t];
-        int buf = 0;
-        for (uint32_t k = 2; k <= (uint32_t)kBins; k <<= 1) {
-            for (uint32_t j = k >> 1; j > 0; j >>= 1) {
-                uint64_t o;
-                if (j >= 64) {
-                    uint64_t* kb = buf ? lb : la;
-                    kb[t] = v;
-                    __syncthreads();
-                    o = kb[t ^ j];
-                    buf ^= 1;
-                } else {
-                    o = __shfl_xor(v, (int)j, 64);
-                }
-                const bool keep_min = ((t & j) == 0) == ((t & k) == 0);
-                v = keep_min ? (o < v ? o : v) : (o > v ? o : v);
-            }
-        }
-        key[t] = v;
-        for (int l = 0; l <= kLmax; l++)
-            if (t < 64) mask[l][t] = 0;
+        // the used symbols' keys (count << 10 | symbol), compacted, then a
+        // bitonic sort over the next power of two (at least a wave), the
+        // rest filled with the largest key; a thread keeps its key in a
+        // register: partners closer than 64 are exchanged inside the wave,
+        // farther ones through two alternating LDS buffers (one barrier per
+        // such stage)
+        const uint32_t P = n <= 64 ? 64u : 1u << (32 - __clz((int)(n - 1)));
+        if (h > 0) buf[0][before + (uint32_t)__popcll(um & ((1ull << lane) - 1))] = ((uint64_t)h << 10) | t;
         __syncthreads();
-        const uint64_t wleaf = (t < (uint32_t)n) ? (key[t] >> 10) : 0;
-        if (t < (uint32_t)n) {
-            la[t] = wleaf;
-            atomicOr(&mask[kLmax][t >> 5], 1u << (t & 31));
+        uint64_t v = t < n ? buf[0][t] : ~0ull;
+        const bool part = 64 * wave < P;  // wave-uniform
+        if (part) {
+            v = stage_in<2, 1>(v);
+            v = stage_in<4, 2>(v);
+            v = stage_in<4, 1>(v);
+            v = stage_in<8, 4>(v);
+            v = stage_in<8, 2>(v);
+            v = stage_in<8, 1>(v);
+            v = stage_in<16, 8>(v);
+            v = stage_in<16, 4>(v);
+            v = stage_in<16, 2>(v);
+            v = stage_in<16, 1>(v);
+            v = stage_in<32, 16>(v);
+            v = stage_in<32, 8>(v);
+            v = stage_in<32, 4>(v);
+            v = stage_in<32, 2>(v);
+            v = stage_in<32, 1>(v);
+            v = merge_wave(v, wave & 1);
         }
-        uint64_t* cur = la;
-        uint64_t* nxt = lb;
-        uint32_t len_cur = n;
-        __syncthreads();
-        for (int l = kLmax - 1; l >= 1; l--) {
-            const uint32_t np = len_cur / 2;
-            if (t < (uint32_t)n) {
-                // packages strictly lighter than this leaf come before it
-                uint32_t lo = 0, hi = np;
-                while (lo < hi) {
-                    uint32_t mid = (lo + hi) >> 1;
-                    if (cur[2 * mid] + cur[2 * mid + 1] < wleaf) lo = mid + 1;
-                    else hi = mid;
+        int side = 1;
+#pragma unroll 1
+        for (uint32_t k = 128; k <= P; k <<= 1) {
+            const bool down = (64 * wave & k) != 0;
+#pragma unroll 1
+            for (uint32_t j = k >> 1; j >= 64; j >>= 1) {
+                uint64_t* kb = buf[side];
+                if (part) kb[t] = v;
+                __syncthreads();
+                if (part) {
+                    const uint64_t o = kb[t ^ j];
+                    const bool keep_min = ((64 * wave & j) == 0) != down;
+                    v = keep_min ? (o < v ? o : v) : (o > v ? o : v);
                 }
-                const uint32_t r = t + lo;
-                nxt[r] = wleaf;
-                atomicOr(&mask[l][r >> 5], 1u << (r & 31));
+                side ^= 1;
             }
-            if (t < np) {
-                const uint64_t pw = cur[2 * t] + cur[2 * t + 1];
-                // leaves not heavier than this package come before it
-                uint32_t lo = 0, hi = (uint32_t)n;
-                while (lo < hi) {
-                    uint32_t mid = (lo + hi) >> 1;
-                    if ((key[mid] >> 10) <= pw) lo = mid + 1;
-                    else hi = mid;
-                }
-                nxt[t + lo] = pw;
-            }
-            __syncthreads();
-            uint64_t* tmp = cur;
-            cur = nxt;
-            nxt = tmp;
-            len_cur = (uint32_t)n + np;
-        }
-        if (t < 64) {
-            // leaves among the first `take` items of each level: lane =
-            // 32-item word of the level's bitmask, popcounts summed over
-            // the wave
-            uint32_t take = 2 * (uint32_t)n - 2;
-            for (int l = 1; l <= kLmax; l++) {
-                if (take > 2 * kBins - 1) take = 2 * kBins - 1;
-                const uint32_t w0 = 32 * t;
-                const uint32_t w = mask[l][t];
-                uint32_t k = take <= w0 ? 0u : (uint32_t)__popc(take - w0 >= 32 ? w : (w & ((1u << (take - w0)) - 1u)));
-#pragma unroll
-                for (int d = 32; d > 0; d >>= 1) k += __shfl_xor(k, d, 64);
-                if (t == 0) klev[l] = k;
-                take = 2 * (take - k);
-            }
+            if (part) v = merge_wave(v, down);
         }
         __syncthreads();
-        if (t < (uint32_t)n) {
-            uint32_t L = 0;
-            for (int l = 1; l <= kLmax; l++) L += (t < klev[l]) ? 1u : 0u;
-            slen[key[t] & 1023] = (uint8_t)L;
-        }
+        uint32_t L;
+        if (total <= 0xFFFFFFFFull / kLmax)
+            L = package_merge<uint32_t>(t < n ? (uint32_t)(v >> 10) : 0u, n, reinterpret_cast<uint32_t*>(buf[0]),
+                                        reinterpret_cast<uint32_t*>(buf[1]), reinterpret_cast<uint32_t*>(buf[2]), ps);
+        else
+            L = package_merge<uint64_t>(t < n ? v >> 10 : 0ull, n, buf[0], buf[1], buf[2], ps);
+        if (t < n) slen[v & 1023] = (uint8_t)L;
     }
     __syncthreads();
     const uint32_t len = slen[t];
     const uint32_t code = canonical_code(len, cs);
     cw[t] = code | (len << 16);
     // total stream bits = sum count * length
-    uint64_t v = (uint64_t)h * len;
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
-    if ((t & 63) == 0) red[t >> 6] = v;
+    const uint64_t bits = wave_incl_scan64((uint64_t)h * len, add);
+    if (lane == 63) red[wave] = bits;
     if (t < 512) out_lens[t] = (uint8_t)(slen[2 * t] | (slen[2 * t + 1] << 4));
     __syncthreads();
+    hist[t] = h;
+#pragma unroll
+    for (int k = 1; k < kHistCopies; k++) hist[k * kBins + t] = 0;
     if (t == 0) {
         uint64_t s = 0;
+#pragma unroll
         for (int w = 0; w < 16; w++) s += red[w];
         misc->total_bits_cb = s;
     }
