@@ -361,6 +361,9 @@ __device__ __forceinline__ void clear_scratch(uint32_t gid, uint32_t stride, uin
 // (associative and commutative).  Executed by one whole wave: lane i reads
 // the descriptor of tile t-1-i, so one round trip covers 64 predecessors;
 // the payloads up to the nearest inclusive one are reduced across the wave.
+// Each descriptor read goes to memory, past the XCDs' caches, so where many
+// workgroups wait at once a smaller WINDOW (one cache line is 16) and a
+// longer SLEEP between the reads (units of 64 cycles) are faster.
 // The wait on a predecessor is bounded: after the spin limit the tile
 // raises F_TIMEOUT and proceeds, so every wave always exits.  Returns the
 // exclusive prefix in every lane.
@@ -376,7 +379,7 @@ __device__ inline uint64_t wave_reduce64(uint64_t v, Op op) {
     return v;
 }
 
-template <class Op>
+template <int WINDOW = 64, int SLEEP = 1, class Op>
 __device__ inline uint64_t lookback(uint64_t* desc, uint32_t t, uint64_t agg, Op op, uint32_t* flags) {
     const int lane = threadIdx.x & 63;
     if (t == 0) {
@@ -391,7 +394,7 @@ __device__ inline uint64_t lookback(uint64_t* desc, uint32_t t, uint64_t agg, Op
         const int64_t j = base - lane;
         // before tile 0 there is an implicit inclusive prefix of 0
         const uint64_t d =
-            j >= 0 ? __hip_atomic_load(&desc[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kStInc;
+            lane >= WINDOW ? kStAgg : j >= 0 ? __hip_atomic_load(&desc[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kStInc;
         const uint32_t st = (uint32_t)(d >> 62);
         const uint64_t inc = __ballot(st == 2);
         const uint64_t notready = __ballot(st == 0);
@@ -402,13 +405,13 @@ __device__ inline uint64_t lookback(uint64_t* desc, uint32_t t, uint64_t agg, Op
                 if (lane == 0) atomicOr(flags, F_TIMEOUT);
                 break;
             }
-            __builtin_amdgcn_s_sleep(1);
+            __builtin_amdgcn_s_sleep(SLEEP);
             continue;
         }
         const uint64_t v = wave_reduce64(lane <= first ? (d & kPayload) : 0ull, op);
         excl = op(excl, v);
         if (first < 64) break;
-        base -= 64;
+        base -= WINDOW;
     }
     if (lane == 0) __hip_atomic_store(&desc[t], kStInc | op(excl, agg), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return excl;

@@ -307,14 +307,6 @@ __global__ __launch_bounds__(1024) void k_codebook(uint32_t* __restrict__ hist, 
 }
 
 // --------------------------------------------------------------- encode
-// (hi, lo) |= v << sh as 128-bit values, sh in [0, 127], the result fits.
-__device__ __forceinline__ void or_shl128(uint64_t& hi, uint64_t& lo, uint64_t v, uint32_t sh) {
-    const bool upper = sh >= 64;
-    const uint32_t s = sh & 63;
-    hi |= upper ? (v << s) : (s ? (v >> ((64 - s) & 63)) : 0ull);
-    lo |= upper ? 0ull : (v << s);
-}
-
 // words of one tile at most (every value at kLmax bits)
 constexpr int kEncTileWords = kTileBlocks * kBlockElems * kLmax / 32;
 
@@ -333,164 +325,204 @@ __device__ __forceinline__ uint4 load_codes(const uint16_t* __restrict__ codes, 
     return *reinterpret_cast<const uint4*>(&codes[at]);
 }
 
-// The (codeword | length << 16) entries of the 8 codes (0 past the real
-// values) and their bit count.
-__device__ __forceinline__ uint32_t code_entries(const uint4& pk, uint32_t nv, const uint32_t* CW, uint32_t e8[8]) {
-    const uint32_t c8[8] = {pk.x & 0xFFFFu, pk.x >> 16, pk.y & 0xFFFFu, pk.y >> 16,
-                            pk.z & 0xFFFFu, pk.z >> 16, pk.w & 0xFFFFu, pk.w >> 16};
-    uint32_t nb = 0;
+// Single pass over the codes.  A workgroup takes T consecutive 4-block
+// tiles: it reads their codes once (all loads issued together, kept packed
+// in registers), writes the chunk table, publishes the group's bit count and
+// obtains the group's stream offset by a decoupled look-back over groups,
+// then writes the bits tile by tile.  A group publishes its count before it
+// waits, and waits only on groups with lower workgroup index (dispatched
+// before it), so the chain never waits on a workgroup that is not running;
+// the wait is bounded anyway (F_TIMEOUT).
+//
+// A workgroup lives about 18 us, 63% of it waiting: for its codes, the
+// look-back and the barriers between its phases.  The quantiser stores a
+// code as the byte offset of its table entry (8 code), entries are a
+// codeword and a length in two registers, codewords join in pairs of 32
+// bits, and a lane's string is placed by three funnel shifts: 14 vector
+// instructions per value instead of 24, which leaves large fields where they
+// were (1024^3 0.79 ms, 512^3 0.15 ms) and helps small ones, whose workgroups
+// run alone.  What did not help at 1024^3: 12 tiles per group (0.86 ms, the
+// waves 105 instead of 89 registers), 6 (0.95), 5 waves per SIMD forced
+// (0.89), look-back windows of 128 and 256 descriptors (0.95, 1.09); a window
+// of 16 and longer sleeps: 0.86 -> 0.79 (every descriptor read goes to
+// memory).  The bits are written in passes of up to kEncPass tiles; small
+// fields take fewer tiles per group, see encode_tiles.
+constexpr uint32_t kEncPass = 4;
+
+// A lane's 8 codes of a segment with nv real values: the sum of their
+// lengths; all: every lane's segment is full (uniform).
+__device__ __forceinline__ uint2 code_entry(const uint2* CW, uint32_t off) {
+    return *reinterpret_cast<const uint2*>(reinterpret_cast<const uint8_t*>(CW) + off);
+}
+__device__ __forceinline__ uint32_t code_bits(const uint4& pk, uint32_t nv, bool all, const uint2* CW) {
+    const uint32_t o[8] = {pk.x & 0xFFFFu, pk.x >> 16, pk.y & 0xFFFFu, pk.y >> 16,
+                           pk.z & 0xFFFFu, pk.z >> 16, pk.w & 0xFFFFu, pk.w >> 16};
+    uint32_t l[8];
 #pragma unroll
-    for (int i = 0; i < 8; i++) {
-        const uint32_t e = CW[c8[i] & (kBins - 1)];
-        e8[i] = i < (int)nv ? e : 0u;
-        nb += e8[i] >> 16;
+    for (int i = 0; i < 8; i++) l[i] = code_entry(CW, o[i]).y;
+    if (!all) {
+#pragma unroll
+        for (int i = 0; i < 8; i++) l[i] = i < (int)nv ? l[i] : 0u;
     }
-    return nb;
+    return ((l[0] + l[1]) + (l[2] + l[3])) + ((l[4] + l[5]) + (l[6] + l[7]));
 }
 
-// Single pass over the codes.  A workgroup takes kEncTiles consecutive
-// 4-block tiles: it reads their codes once (all loads issued together, kept
-// packed in registers), writes the
-// chunk table, publishes the group's bit count and obtains the group's
-// stream offset by a decoupled look-back over groups, then writes the bits
-// tile by tile.  A group publishes its count before it waits, and waits
-// only on groups with lower workgroup index (dispatched before it), so the
-// chain never waits on a workgroup that is not running; the wait is bounded
-// anyway (F_TIMEOUT).
-// tiles per group: 12 measured fastest at 1024^3 (0.88 ms; 4: 1.21, 8:
-// 0.93, 16: 0.92); the bits are written in passes of kEncPass tiles
-constexpr uint32_t kEncTiles = 12;
-constexpr uint32_t kEncPass = 6;
-constexpr int kEncWords = (int)kEncPass * kEncTileWords + 8;  // one pass (+ bit offset and window overrun)
-
-template <int ND>
+template <int ND, uint32_t T>
 __global__ __launch_bounds__(256) void k_encode(const uint16_t* __restrict__ codes, Geom g,
                                                 const uint32_t* __restrict__ cw_g, uint32_t ntiles, Misc* misc,
                                                 uint8_t* __restrict__ out, uint64_t* desc,
                                                 uint64_t* __restrict__ tile_start, uint32_t* __restrict__ tfirst,
                                                 uint32_t* __restrict__ tlast) {
-    __shared__ uint32_t CW[kBins];
-    __shared__ uint32_t W[kEncWords];  // one pass of tiles
-    __shared__ uint32_t s_carry[2];    // a pass's partial last word, for the next pass (by pass parity)
-    __shared__ uint32_t wsum[kEncTiles][4];
+    constexpr uint32_t kPass = T < kEncPass ? T : kEncPass;
+    static_assert(T % kPass == 0, "whole passes");
+    constexpr int kWords = (int)kPass * kEncTileWords + 8;  // one pass (+ bit offset and window overrun)
+    __shared__ uint2 CW[kBins];
+    __shared__ uint32_t W[kWords];   // one pass of tiles
+    __shared__ uint32_t s_carry[2];  // a pass's partial last word, for the next pass (by pass parity)
+    __shared__ uint32_t wsum[T][4];
     __shared__ uint64_t s_excl;
+    // an error bound the quantiser rejected: it wrote no codes, and what the
+    // buffer holds are no table offsets (set before this kernel, so the same
+    // for every workgroup)
+    if (misc->flags & F_EB) return;
     uint16_t* chunks = reinterpret_cast<uint16_t*>(out + misc->off_chunks);
     uint32_t* stream = reinterpret_cast<uint32_t*>(out + misc->off_stream);
     const uint32_t t = threadIdx.x, lane = t & 63;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(t >> 6));
-    for (uint32_t i = t; i < (uint32_t)kBins; i += 256) CW[i] = cw_g[i];
-    for (uint32_t i = t; i < (uint32_t)kEncWords; i += 256) W[i] = 0;
-    __syncthreads();
     const uint32_t grp = blockIdx.x;
-    const uint32_t tile0 = grp * kEncTiles;
+    const uint32_t tile0 = grp * T;
     // pass over the group's codes: every tile's codes loaded at once
     // (packed, 4 registers per tile, so the loads' latencies overlap), then
     // the tiles' bit counts and totals; the codeword entries are looked up
     // again when the bits are written
-    uint4 pk[kEncTiles];
-    uint32_t nvk[kEncTiles];
+    uint4 pk[T];
+    uint32_t partial = 0;             // tiles where some lane's segment is not full (uniform)
+    uint32_t pre[(T + 1) / 2] = {};   // bits of the wave's earlier lanes, two tiles per register
 #pragma unroll
-    for (uint32_t k = 0; k < kEncTiles; k++) {
+    for (uint32_t k = 0; k < T; k++) {
+        uint32_t nv;
         const uint32_t b = (tile0 + k) * kTileBlocks + wave;
-        pk[k] = load_codes<ND>(codes, g, tile0 + k < ntiles ? b : g.nblocks, lane, nvk[k]);
+        pk[k] = load_codes<ND>(codes, g, tile0 + k < ntiles ? b : g.nblocks, lane, nv);
+        partial |= (__ballot(nv != 8) ? 1u : 0u) << k;
     }
+    // real values of the lane's segment, again where they are not 8
+    auto real_values = [&](uint32_t k) -> uint32_t {
+        const uint32_t b = (tile0 + k) * kTileBlocks + wave;
+        uint32_t nv = 0;
+        if (tile0 + k < ntiles && b < g.nblocks) {
+            const BlockInfo info = block_info(g, b);
+            seg_index<ND>(g, info, lane, nv);
+        }
+        return nv;
+    };
+    for (uint32_t i = t; i < (uint32_t)kBins; i += 256) {
+        const uint32_t e = cw_g[i];
+        CW[i] = make_uint2(e & 0xFFFFu, e >> 16);
+    }
+    for (uint32_t i = t; i < (uint32_t)kWords; i += 256) W[i] = 0;
+    __syncthreads();
 #pragma unroll
-    for (uint32_t k = 0; k < kEncTiles; k++) {
-        uint32_t e8[8];
-        const uint32_t nb = tile0 + k < ntiles ? code_entries(pk[k], nvk[k], CW, e8) : 0u;
+    for (uint32_t k = 0; k < T; k++) {
+        const bool all = !((partial >> k) & 1u);
+        const uint32_t nb = code_bits(pk[k], all ? 8u : real_values(k), all, CW);
         const uint32_t incl = wave_incl_scan(nb);
+        pre[k / 2] |= (incl - nb) << (16 * (k & 1));  // at most 6144
         if (lane == 63) wsum[k][wave] = incl;
     }
     __syncthreads();
     // chunk table (block bit counts) from the tile totals: no store among
     // the phase's loads, whose waits would otherwise also cover it
-    if (t < kEncTiles * 4) {
+    if (t < T * 4) {
         const uint32_t k = t >> 2, w = t & 3;
         const uint32_t b = (tile0 + k) * kTileBlocks + w;
         if (tile0 + k < ntiles && b < g.nblocks) chunks[b] = (uint16_t)wsum[k][w];
     }
     uint64_t gsum = 0;
-    for (uint32_t k = 0; k < kEncTiles; k++) gsum += wsum[k][0] + wsum[k][1] + wsum[k][2] + wsum[k][3];
+    for (uint32_t k = 0; k < T; k++) gsum += wsum[k][0] + wsum[k][1] + wsum[k][2] + wsum[k][3];
     if (wave == 0) {
-        const uint64_t ex = lookback(desc, grp, gsum, OpAdd(), &misc->flags);
+        const uint64_t ex = lookback<16, 8>(desc, grp, gsum, OpAdd(), &misc->flags);
         if (lane == 0) {
             s_excl = ex;
-            if (tile0 + kEncTiles >= ntiles) misc->total_bits_enc = ex + gsum;
+            if (tile0 + T >= ntiles) misc->total_bits_enc = ex + gsum;
         }
     }
     __syncthreads();
-    // the bits, in passes of kEncPass tiles: each pass's tiles are OR-ed
-    // into one LDS buffer (one barrier), then its words are stored as one
+    // the bits, in passes of kPass tiles: each pass's tiles are OR-ed into
+    // one LDS buffer (one barrier), then its words are stored as one
     // contiguous run.  The group's partial first and last words are shared
     // with the neighbouring groups and merged by k_finalize (tile_start of
     // the group's first tile; its other tiles start at 0, nothing to
     // merge); a pass's partial last word is carried into the next pass.
     const uint64_t G0 = s_excl;
-    const uint32_t tend = min(tile0 + kEncTiles, ntiles);  // past the group's last tile
-    if (t < kEncTiles && tile0 + t < ntiles) tile_start[tile0 + t] = t == 0 ? G0 : 0ull;
+    const uint32_t tend = min(tile0 + T, ntiles);  // past the group's last tile
+    if (t < T && tile0 + t < ntiles) tile_start[tile0 + t] = t == 0 ? G0 : 0ull;
     uint64_t G = G0;
 #pragma unroll
-    for (uint32_t h = 0; h < kEncTiles / kEncPass; h++) {
-        const uint32_t k0 = h * kEncPass;
+    for (uint32_t h = 0; h < T / kPass; h++) {
+        const uint32_t k0 = h * kPass;
         if (tile0 + k0 >= ntiles) break;  // uniform
         const uint32_t shp = (uint32_t)(G & 31);
         uint32_t rel = 0;  // bits of the pass's earlier tiles
 #pragma unroll
-        for (uint32_t kk = 0; kk < kEncPass; kk++) {
+        for (uint32_t kk = 0; kk < kPass; kk++) {
             const uint32_t k = k0 + kk;
             const uint32_t tile = tile0 + k;
             if (tile >= ntiles) break;  // uniform
-            uint32_t wpre = 0, T = 0;
+            uint32_t wpre = 0, bits = 0;
             for (uint32_t w = 0; w < 4; w++) {
                 if (w < wave) wpre += wsum[k][w];
-                T += wsum[k][w];
+                bits += wsum[k][w];
             }
-            if (t == 0 && tile != ntiles - 1 && T < 32) atomicOr(&misc->flags, F_INTERNAL);
-            // the lane's bit string as two shift-or chains of 4 codewords
-            // (at most 48 bits each)
-            uint32_t e8[8];
-            code_entries(pk[k], nvk[k], CW, e8);
-            uint64_t a0 = 0, a1 = 0;
-            uint32_t n0 = 0, n1 = 0;
+            if (t == 0 && tile != ntiles - 1 && bits < 32) atomicOr(&misc->flags, F_INTERNAL);
+            // (keeps the first pass's eight offsets per tile from being held
+            // in registers until here: 162 VGPRs, three waves per SIMD)
+            asm volatile("" : "+v"(pk[k].x), "+v"(pk[k].y), "+v"(pk[k].z), "+v"(pk[k].w));
+            const uint32_t o8[8] = {pk[k].x & 0xFFFFu, pk[k].x >> 16, pk[k].y & 0xFFFFu, pk[k].y >> 16,
+                                    pk[k].z & 0xFFFFu, pk[k].z >> 16, pk[k].w & 0xFFFFu, pk[k].w >> 16};
+            uint2 e8[8];
 #pragma unroll
-            for (int i = 0; i < 4; i++) {
-                const uint32_t e = e8[i], l = e >> 16;
-                a0 = (a0 << l) | (e & 0xFFFFu);
-                n0 += l;
-            }
+            for (int i = 0; i < 8; i++) e8[i] = code_entry(CW, o8[i]);
+            uint32_t nv = 8;
+            if ((partial >> k) & 1u) {  // uniform
+                nv = real_values(k);
 #pragma unroll
-            for (int i = 4; i < 8; i++) {
-                const uint32_t e = e8[i], l = e >> 16;
-                a1 = (a1 << l) | (e & 0xFFFFu);
-                n1 += l;
+                for (int i = 0; i < 8; i++)
+                    if (i >= (int)nv) e8[i] = make_uint2(0, 0);
             }
-            const uint32_t nb = n0 + n1;
-            // the scan runs with every lane active (lanes with no bits add 0)
-            const uint32_t incl = wave_incl_scan(nb);
-            if (nb) {
-                // place the string at bit o of word w0 (from the pass's
-                // first word), most significant first: 128-bit window
-                // (hi, lo) = words w0 .. w0 + 3 (o + nb <= 127)
-                const uint32_t p = shp + rel + wpre + incl - nb;
+            if (nv) {
+                // pairs (at most 24 bits), then the lane's two strings of 4
+                // codewords (at most 48 bits)
+                uint32_t pr[4], pl[4];
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    pr[i] = e8[2 * i].x << e8[2 * i + 1].y | e8[2 * i + 1].x;
+                    pl[i] = e8[2 * i].y + e8[2 * i + 1].y;
+                }
+                const uint64_t a0 = (uint64_t)pr[0] << pl[1] | pr[1], a1 = (uint64_t)pr[2] << pl[3] | pr[3];
+                const uint32_t n0 = pl[0] + pl[1], n1 = pl[2] + pl[3];  // n0 >= 1; a1 = 0 when n1 = 0
+                // left-aligned in three words, then shifted right by the bit
+                // offset o into words w0 .. w0 + 3 (o + n0 + n1 <= 127)
+                const uint64_t b1 = a1 << ((64 - n1) & 63);
+                const uint64_t s01 = a0 << (64 - n0) | b1 >> n0;
+                const uint32_t s2 = (uint32_t)((b1 << (64 - n0)) >> 32);
+                const uint32_t s0 = (uint32_t)(s01 >> 32), s1 = (uint32_t)s01;
+                const uint32_t p = shp + rel + wpre + ((pre[k / 2] >> (16 * (k & 1))) & 0xFFFFu);  // from the pass's first word
                 const uint32_t o = p & 31, w0 = p >> 5;
-                uint64_t hi = 0, lo = 0;
-                or_shl128(hi, lo, a0, (128 - o - n0) & 127);  // a0 = 0 when n0 = 0
-                or_shl128(hi, lo, a1, 128 - o - nb);
-                const uint32_t o0 = (uint32_t)(hi >> 32), o1 = (uint32_t)hi, o2 = (uint32_t)(lo >> 32),
-                               o3 = (uint32_t)lo;
-                if (o0) atomicOr(&W[w0], o0);
+                const uint32_t o0 = s0 >> o, o1 = __builtin_amdgcn_alignbit(s0, s1, o),
+                               o2 = __builtin_amdgcn_alignbit(s1, s2, o), o3 = __builtin_amdgcn_alignbit(s2, 0, o);
+                atomicOr(&W[w0], o0);
                 if (o1) atomicOr(&W[w0 + 1], o1);
                 if (o2) atomicOr(&W[w0 + 2], o2);
                 if (o3) atomicOr(&W[w0 + 3], o3);
             }
-            rel += T;
+            rel += bits;
         }
         __syncthreads();
         // the pass's words: the first one shares bits with the previous
         // pass (carried) or group (parked in tfirst), the last one with the
         // next pass (carried) or group (parked in tlast of the group's last
         // tile); the field's very last word is stored
-        const bool last_pass = tile0 + k0 + kEncPass >= tend;
+        const bool last_pass = tile0 + k0 + kPass >= tend;
         const uint32_t nwords = (shp + rel + 31) >> 5;
         const bool end_part = ((shp + rel) & 31) != 0;
         const uint64_t wbase = G >> 5;
@@ -718,23 +750,40 @@ void launch_codebook(hipStream_t st, uint32_t* hist, uint8_t* out_lens, uint32_t
     hipLaunchKernelGGL(k_codebook, dim3(1), dim3(1024), 0, st, hist, out_lens, cw, misc);
 }
 
+// Tiles per group: a group's tiles are worked off one after the other, so a
+// field with few tiles is split further.  Measured, 3D fields (us, 12 per
+// group / this rule): 128 tiles 19.1 / 10.7, 1024 20.6 / 14.6, 3456 24.1 /
+// 21.1, 8192 30.1 / 30.4; 1 and 2 per group 17.2 and 15.3 at 1024 tiles, 33
+// and 24 at 3456 (the look-back chain grows with the groups).
+static uint32_t encode_tiles(uint32_t ntiles) { return ntiles >= 6144 ? 8u : (ntiles >= 256 ? 4u : 1u); }
+
 void launch_encode(hipStream_t st, int grid, const uint16_t* codes, const Geom& g, const uint32_t* cw, Misc* misc,
                    uint32_t ntiles, uint8_t* out, uint64_t* desc, uint64_t* tile_start, uint32_t* tfirst,
                    uint32_t* tlast) {
     (void)grid;  // one workgroup per group of tiles
-    const uint32_t groups = (ntiles + kEncTiles - 1) / kEncTiles;
-    if (g.ndim == 3)
-        hipLaunchKernelGGL(k_encode<3>, dim3(groups), dim3(256), 0, st, codes, g, cw, ntiles, misc, out, desc,
-                           tile_start, tfirst, tlast);
-    else if (g.ndim == 2)
-        hipLaunchKernelGGL(k_encode<2>, dim3(groups), dim3(256), 0, st, codes, g, cw, ntiles, misc, out, desc,
-                           tile_start, tfirst, tlast);
-    else
-        hipLaunchKernelGGL(k_encode<1>, dim3(groups), dim3(256), 0, st, codes, g, cw, ntiles, misc, out, desc,
-                           tile_start, tfirst, tlast);
+    const uint32_t groups = encode_groups(ntiles), T = encode_tiles(ntiles);
+#define FZ_ENC(NDV, TV)                                                                                             \
+    hipLaunchKernelGGL((k_encode<NDV, TV>), dim3(groups), dim3(256), 0, st, codes, g, cw, ntiles, misc, out, desc, \
+                       tile_start, tfirst, tlast)
+#define FZ_ENC_T(NDV)            \
+    if (T == 8) FZ_ENC(NDV, 8); \
+    else if (T == 4) FZ_ENC(NDV, 4); \
+    else FZ_ENC(NDV, 1)
+    if (g.ndim == 3) {
+        FZ_ENC_T(3);
+    } else if (g.ndim == 2) {
+        FZ_ENC_T(2);
+    } else {
+        FZ_ENC_T(1);
+    }
+#undef FZ_ENC_T
+#undef FZ_ENC
 }
 
-uint32_t encode_groups(uint32_t ntiles) { return (ntiles + kEncTiles - 1) / kEncTiles; }
+uint32_t encode_groups(uint32_t ntiles) {
+    const uint32_t T = encode_tiles(ntiles);
+    return (ntiles + T - 1) / T;
+}
 
 void launch_finalize(hipStream_t st, const Geom& g, uint32_t mode, double eb, uint32_t pred, Misc* misc,
                      uint8_t* out, uint32_t ntiles, const uint64_t* tile_start, const uint32_t* tfirst,

@@ -956,11 +956,12 @@ __global__ __launch_bounds__(256) void k_quant(const float* __restrict__ x, Geom
             if (w[1]) S[kMaskWords + c0 + __popcll(m1 & below)] = w[1];
             if (w[2]) S[kMaskWords + c0 + c1 + __popcll(m2 & below)] = w[2];
         } else if (blk) {
+            // 8 code: the byte offset of the encoder's table entry
             uint4 pk;
-            pk.x = code[0] | (code[1] << 16);
-            pk.y = code[2] | (code[3] << 16);
-            pk.z = code[4] | (code[5] << 16);
-            pk.w = code[6] | (code[7] << 16);
+            pk.x = (code[0] | (code[1] << 16)) << 3;
+            pk.y = (code[2] | (code[3] << 16)) << 3;
+            pk.z = (code[4] | (code[5] << 16)) << 3;
+            pk.w = (code[6] | (code[7] << 16)) << 3;
             *reinterpret_cast<uint4*>(&codes[(uint64_t)b * kBlockElems + s * 8]) = pk;
         }
         // histogram: the zero residual's code (the most frequent one in
