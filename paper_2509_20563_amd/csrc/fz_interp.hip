@@ -5,7 +5,9 @@
 // prediction needs (fz_common.h, interp_predict), one launch per stride and
 // axis:
 //   k_interp_anchor  - prefix sums along one axis of the anchor grid (every
-//                      coordinate a multiple of 8), one thread per line
+//                      coordinate a multiple of 8), one wave per line; long
+//                      lines in segments (k_interp_anchor_sums, _offsets,
+//                      _segs)
 //   k_interp_level_z, k_interp_level_yx - strides 4 and 2 (2D/3D): the
 //                      stride-1 passes below on the lattice of that stride,
 //                      in place
@@ -25,49 +27,109 @@
 
 namespace fz {
 
-// Position of (x, y, z) in the row-major residual and grid-value fields.
-template <int ND>
-__device__ __forceinline__ uint64_t rm_index(const Geom& g, uint32_t x, uint32_t y, uint32_t z) {
-    return (uint64_t)x + (uint64_t)g.n[0] * ((uint64_t)y + (uint64_t)g.n[1] * z);
-}
+// Prefix sums along one axis of the anchor grid (every coordinate a
+// multiple of 8), in place.  Latency-bound: an anchor is a cache line of its
+// own, and a line of anchors is a serial chain.  A wave takes one line, 64
+// anchors per step as a DPP scan, kAnchorBatch steps' loads issued at once
+// (in place, a load cannot move above an earlier store by itself).  512^3:
+// 7 us per axis, 11 us with a thread per line.  Lines of more than
+// kAnchorLong anchors (1D, long 2D rows), which a wave would follow for
+// long, are cut into segments: sums per segment, a scan of these, then the
+// segments (34 M values of a 1D field decompress in 0.39 ms; one thread
+// followed that line for 300 ms).
+constexpr int kAnchorBatch = 4;
+constexpr uint32_t kAnchorLong = 2048, kAnchorSeg = 512;
 
-// Number of coordinates c < n with c = first + step k.
-__device__ __forceinline__ uint32_t n_coords(uint32_t n, uint32_t first, uint32_t step) {
-    return n > first ? (n - first + step - 1) / step : 0u;
-}
+// Lines of the axis: number of anchors, distance between two, and the first
+// one of line l.
+struct AnchorLines {
+    uint32_t len, lc0, lc1;
+    uint64_t nlines, step, s0, s1, s2;  // s*: distance of neighbouring anchors per axis
+    __device__ __forceinline__ uint64_t first(uint64_t l) const {
+        const uint64_t a = l / lc0;
+        return s0 * (l - a * lc0) + s1 * (a % lc1) + s2 * (a / lc1);
+    }
+};
 
-// Loads of one anchor line issued together (the line is read and written
-// in place, so a load cannot move above an earlier store by itself)
-constexpr int kAnchorBatch = 16;
-
-template <int ND>
-__global__ __launch_bounds__(64) void k_interp_anchor(Geom g, const int32_t* src, int32_t* dst, int axis) {
-    // lines: the anchor coordinates of the other axes
-    uint32_t cnt[3] = {1, 1, 1};
-    for (int a = 0; a < ND; a++) cnt[a] = n_coords(g.n[a], 0, 8);
-    uint32_t lc[3] = {cnt[0], cnt[1], cnt[2]};
-    lc[axis] = 1;
-    const uint64_t nlines = (uint64_t)lc[0] * lc[1] * lc[2];
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    const uint64_t sa = 8 * (axis == 0 ? 1ull : (axis == 1 ? (uint64_t)g.n[0] : (uint64_t)g.n[0] * g.n[1]));
-    const uint32_t len = cnt[axis];
-    for (uint64_t l = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; l < nlines; l += stride) {
-        uint32_t c[3] = {(uint32_t)(l % lc[0]) * 8, (uint32_t)((l / lc[0]) % lc[1]) * 8,
-                         (uint32_t)(l / ((uint64_t)lc[0] * lc[1])) * 8};
-        c[axis] = 0;
-        const uint64_t i0 = rm_index<ND>(g, c[0], c[1], c[2]);
-        int32_t acc = 0;
-        for (uint32_t k0 = 0; k0 < len; k0 += kAnchorBatch) {
-            int32_t v[kAnchorBatch];
+// `count` anchors from index i0 on: inclusive sums in place, from `acc` on
+// (whole wave); the new total.
+__device__ __forceinline__ uint32_t anchor_scan(int32_t* q, uint64_t i0, uint64_t step, uint32_t count, uint32_t acc) {
+    const uint32_t lane = threadIdx.x & 63;
+    for (uint32_t k0 = 0; k0 < count; k0 += 64 * kAnchorBatch) {
+        uint32_t v[kAnchorBatch];
 #pragma unroll
-            for (int j = 0; j < kAnchorBatch; j++) v[j] = k0 + j < len ? src[i0 + sa * (k0 + j)] : 0;
+        for (int j = 0; j < kAnchorBatch; j++) {
+            const uint32_t k = k0 + 64 * j + lane;
+            v[j] = k < count ? (uint32_t)q[i0 + step * k] : 0u;
+        }
 #pragma unroll
-            for (int j = 0; j < kAnchorBatch; j++) {
-                acc = (int32_t)((uint32_t)acc + (uint32_t)v[j]);
-                if (k0 + j < len) dst[i0 + sa * (k0 + j)] = acc;
-            }
+        for (int j = 0; j < kAnchorBatch; j++) {
+            const uint32_t k = k0 + 64 * j + lane;
+            const uint32_t s = wave_incl_scan(v[j]) + acc;
+            if (k < count) q[i0 + step * k] = (int32_t)s;
+            acc = (uint32_t)__builtin_amdgcn_readlane((int)s, 63);
         }
     }
+    return acc;
+}
+
+__global__ __launch_bounds__(256) void k_interp_anchor(int32_t* q, AnchorLines L) {
+    const uint64_t l = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (l < L.nlines) anchor_scan(q, L.first(l), L.step, L.len, 0u);
+}
+
+// Segment sums of the lines (wave = segment; sums[line][segment])
+__global__ __launch_bounds__(256) void k_interp_anchor_sums(const int32_t* __restrict__ q, AnchorLines L,
+                                                            uint32_t nseg, uint32_t* __restrict__ sums) {
+    const uint32_t lane = threadIdx.x & 63;
+    const uint64_t u = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (u >= L.nlines * nseg) return;
+    const uint64_t l = u / nseg;
+    const uint32_t at = (uint32_t)(u - l * nseg) * kAnchorSeg;
+    const uint64_t i0 = L.first(l);
+    uint32_t a = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < kAnchorSeg / 64; j++) {
+        const uint32_t k = at + 64 * j + lane;
+        a += k < L.len ? (uint32_t)q[i0 + L.step * k] : 0u;
+    }
+    a = wave_incl_scan(a);
+    if (lane == 63) sums[u] = a;
+}
+
+// Exclusive scan of each line's segment sums, in place (workgroup = line)
+__global__ __launch_bounds__(1024) void k_interp_anchor_offsets(uint64_t nlines, uint32_t nseg,
+                                                                uint32_t* __restrict__ sums) {
+    __shared__ uint32_t ws[16];
+    const uint32_t t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    for (uint64_t l = blockIdx.x; l < nlines; l += gridDim.x) {
+        uint32_t* S = sums + l * nseg;
+        uint32_t acc = 0;
+        for (uint32_t k0 = 0; k0 < nseg; k0 += 1024) {
+            const uint32_t v = k0 + t < nseg ? S[k0 + t] : 0u;
+            const uint32_t incl = wave_incl_scan(v);
+            __syncthreads();
+            if (lane == 63) ws[wave] = incl;
+            __syncthreads();
+            uint32_t before = acc, total = 0;
+#pragma unroll
+            for (uint32_t w = 0; w < 16; w++) {
+                before += w < wave ? ws[w] : 0u;
+                total += ws[w];
+            }
+            if (k0 + t < nseg) S[k0 + t] = before + incl - v;
+            acc += total;
+        }
+    }
+}
+
+__global__ __launch_bounds__(256) void k_interp_anchor_segs(int32_t* q, AnchorLines L, uint32_t nseg,
+                                                            const uint32_t* __restrict__ offs) {
+    const uint64_t u = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (u >= L.nlines * nseg) return;
+    const uint64_t l = u / nseg;
+    const uint32_t at = (uint32_t)(u - l * nseg) * kAnchorSeg;
+    anchor_scan(q, L.first(l) + L.step * at, L.step, min(kAnchorSeg, L.len - at), offs[u]);
 }
 
 // Prediction of a point at coordinate c along its axis (field extent n,
@@ -471,22 +533,44 @@ __global__ __launch_bounds__(256) void k_interp_final_yx(Geom g, const int32_t* 
     }
 }
 
-template <int ND>
-static void interp_anchors(hipStream_t st, const Geom& g, const int32_t* src, int32_t* dst) {
-    uint32_t acnt[3] = {1, 1, 1};
-    for (int a = 0; a < ND; a++) acnt[a] = (g.n[a] + 7) / 8;
-    for (int a = 0; a < ND; a++) {
-        uint64_t lines = (uint64_t)acnt[0] * acnt[1] * acnt[2] / acnt[a];
-        uint64_t gr = (lines + 63) / 64;
-        if (gr > 32768) gr = 32768;
-        hipLaunchKernelGGL(k_interp_anchor<ND>, dim3((uint32_t)gr), dim3(64), 0, st, g, a ? dst : src, dst, a);
+// `out` (the field, written by the last pass) holds the segment sums of long
+// lines until then: at most one per kAnchorSeg anchors.
+static void interp_anchors(hipStream_t st, const Geom& g, int32_t* q, float* out) {
+    const uint64_t sa[3] = {8, 8ull * g.n[0], 8ull * g.n[0] * g.n[1]};
+    uint32_t c[3];
+    for (int a = 0; a < 3; a++) c[a] = (g.n[a] + 7) / 8;
+    for (int a = 0; a < (int)g.ndim; a++) {
+        // the other axes number the lines, the faster one first
+        uint32_t lc[3] = {c[0], c[1], c[2]};
+        lc[a] = 1;
+        AnchorLines L;
+        L.len = c[a];
+        L.step = sa[a];
+        L.lc0 = lc[0];
+        L.lc1 = lc[1];
+        L.nlines = (uint64_t)lc[0] * lc[1] * lc[2];
+        L.s0 = sa[0];
+        L.s1 = sa[1];
+        L.s2 = sa[2];
+        if (L.len < 2) continue;
+        if (L.len <= kAnchorLong) {
+            hipLaunchKernelGGL(k_interp_anchor, dim3((uint32_t)((L.nlines + 3) / 4)), dim3(256), 0, st, q, L);
+            continue;
+        }
+        const uint32_t nseg = (L.len + kAnchorSeg - 1) / kAnchorSeg;
+        uint32_t* sums = reinterpret_cast<uint32_t*>(out);
+        const uint32_t grid = (uint32_t)((L.nlines * nseg + 3) / 4);
+        hipLaunchKernelGGL(k_interp_anchor_sums, dim3(grid), dim3(256), 0, st, q, L, nseg, sums);
+        hipLaunchKernelGGL(k_interp_anchor_offsets, dim3((uint32_t)(L.nlines < 4096 ? L.nlines : 4096)), dim3(1024),
+                           0, st, L.nlines, nseg, sums);
+        hipLaunchKernelGGL(k_interp_anchor_segs, dim3(grid), dim3(256), 0, st, q, L, nseg, sums);
     }
 }
 
 // 1D and 2D: one pass per stride and axis, in place on the residuals
 template <int ND>
 static void interp_inverse_passes(hipStream_t st, const Geom& g, int32_t* q, double e2, float* out) {
-    interp_anchors<ND>(st, g, q, q);
+    interp_anchors(st, g, q, out);
     auto cap = [](uint64_t r) { return (uint32_t)(r < 65535 ? r : 65535); };
     for (uint32_t s = 4; s >= 2; s >>= 1) {
         if (ND >= 2) {
