@@ -96,6 +96,52 @@ __device__ __forceinline__ void load_map(uint32_t t, uint32_t& bi, uint32_t& s) 
     else { bi = t >> 6; s = t & 63; }                                     // contiguous
 }
 
+// Prequantisation: the same q as prequant1, with its two tests for a lossless
+// patch in float against bounds a little inside the exact ones (thr: |x - xh|
+// rounds to at most thr only if it is at most eb; bigthr: |x| below it means
+// |x / 2eb| below 2^24).  The lanes of a value outside either (a patch, a value
+// close to one, no finite value) are collected, and their wave repeats its
+// values with prequant1.  (50 M values of a 1D field: 92 us with the double
+// tests, 83 so.)
+struct FastQuant {
+    double e2, inv, eb_abs;
+    float thr, bigthr;
+    __device__ __forceinline__ void init(double eb) {
+        eb_abs = eb;
+        e2 = 2.0 * eb;
+        inv = 1.0 / e2;
+        // below 1e-37 the float bounds lose their relative precision: no
+        // value passes
+        const double t = eb * (1.0 - 0x1p-22), b = 0x1p24 * e2 * (1.0 - 0x1p-20);
+        thr = uniform(t < 1e-37 ? -1.0f : down(t));
+        bigthr = uniform(b < 1e-37 ? -1.0f : down(b));
+        eb_abs = uniform(eb_abs);
+        e2 = uniform(e2);
+        inv = uniform(inv);
+    }
+    // the same in every lane: held in scalar registers
+    static __device__ __forceinline__ float uniform(float v) {
+        return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+    }
+    static __device__ __forceinline__ double uniform(double v) {
+        return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
+                                __builtin_amdgcn_readfirstlane(__double2loint(v)));
+    }
+    // the largest float not above v > 0
+    static __device__ __forceinline__ float down(double v) {
+        if (v >= 3.4028234663852886e38) return 3.4028234663852886e38f;
+        float f = (float)v;
+        return (double)f > v ? __uint_as_float(__float_as_uint(f) - 1) : f;
+    }
+    // q of x; `odd`: the lanes whose value the exact test has to see
+    __device__ __forceinline__ int32_t operator()(float x, uint64_t& odd) const {
+        const double r = __builtin_rint((double)x * inv);
+        const float d = x - (float)(r * e2);
+        odd |= __ballot(!(__builtin_fabsf(d) <= thr)) | __ballot(!(__builtin_fabsf(x) < bigthr));
+        return (int32_t)r;
+    }
+};
+
 // ------------------------------------------- fused Lorenzo quantisation
 // One workgroup (256 threads) handles a tile of 4 consecutive blocks per
 // iteration (tiles assigned statically, grid-strided).
@@ -251,8 +297,19 @@ __device__ __forceinline__ void global_halo_at(uint32_t e, uint32_t& bi, int& dx
 // kept words in order).
 constexpr int kQuantP0 = 0, kQuantPred = 1, kQuantTrial = 2, kQuantInterp = 3, kQuantGlobal = 4, kQuantShuffle = 5;
 
+// Waves per SIMD the registers have to allow.  The halo of the 3D predictors
+// costs registers: without a bound the interpolation kernel took 170 (two
+// waves per SIMD: 561 us for 512^3 values; 453 at three, 510 at four, which
+// spills), the global one 133 (three: 502 us for 26 x 1800 x 3600; 461 at
+// four, 659 at five).  The others are not bound by it (first-order 3D:
+// 1642 us for 1024^3 values at five waves, 1672 at six with 12 B of spills,
+// 2523 at eight).
+constexpr int quant_waves(int nd, int mode) {
+    return nd != 3 ? 1 : (mode == kQuantInterp ? 3 : (mode == kQuantGlobal ? 4 : 1));
+}
+
 template <int ND, int MODE>
-__global__ __launch_bounds__(256) void k_quant(const float* __restrict__ x, Geom g, uint32_t mode, double eb,
+__global__ __launch_bounds__(256, quant_waves(ND, MODE)) void k_quant(const float* __restrict__ x, Geom g, uint32_t mode, double eb,
                                                int vec, Misc* misc, uint32_t* __restrict__ hist_g,
                                                uint16_t* __restrict__ codes, uint32_t ntiles,
                                                uint32_t* __restrict__ tile_cnt, uint2* __restrict__ ostage,
@@ -294,8 +351,10 @@ __global__ __launch_bounds__(256) void k_quant(const float* __restrict__ x, Geom
         if (blockIdx.x == 0 && t == 0) atomicOr(&misc->flags, F_EB);
         return;
     }
-    const double e2 = 2.0 * eb_abs;
-    const double inv = 1.0 / e2;
+    FastQuant fq;
+    fq.init(eb_abs);
+    const double e2 = fq.e2, inv = fq.inv;
+    eb_abs = fq.eb_abs;
     // under the value-range bound the min/max pass has already flagged
     // non-finite input; the absolute bound has no such pass
     const bool check_finite = mode != 1;
@@ -320,12 +379,13 @@ __global__ __launch_bounds__(256) void k_quant(const float* __restrict__ x, Geom
     seg_coords<ND>(la_s, la_lx0, la_ly, la_lz);
     const uint32_t la_rowoff = la_lx0 + g.n[0] * (la_ly + g.n[1] * la_lz);
     // 3D interpolation and 3D global Lorenzo: this thread's halo entries
-    // t + 256 k, decoded once (block of the tile in bits 0-1, dx + 8, dy + 8,
-    // dz + 8 in 5 bits each)
+    // t + 256 k, decoded once: position relative to the tile's first block
+    // plus 8 in bytes (x, y, z; the block of the tile in the fourth byte, its
+    // origin 8 further in x each), and the row-major offset from that origin
     constexpr bool kHalo3 = (MODE == kQuantInterp || MODE == kQuantGlobal) && ND == 3;
     constexpr int kHaloN = MODE == kQuantInterp ? kTileBlocks * kIHB + kIHX : kTileBlocks * kHB + kHL;
     constexpr int kIHPerThread = kHalo3 ? (kHaloN + 255) / 256 : 1;
-    uint32_t ih_code[kIHPerThread];
+    uint32_t ih_code[kIHPerThread], ih_off[kIHPerThread];
     if (kHalo3) {
 #pragma unroll
         for (int k = 0; k < kIHPerThread; k++) {
@@ -336,7 +396,9 @@ __global__ __launch_bounds__(256) void k_quant(const float* __restrict__ x, Geom
                 if (MODE == kQuantInterp) interp_halo_at(e, bi, dx, dy, dz);
                 else global_halo_at(e, bi, dx, dy, dz);
             }
-            ih_code[k] = bi | (uint32_t)(dx + 8) << 2 | (uint32_t)(dy + 8) << 7 | (uint32_t)(dz + 8) << 12;
+            dx += 8 * (int)bi;
+            ih_code[k] = bi << 24 | (uint32_t)(dz + 8) << 16 | (uint32_t)(dy + 8) << 8 | (uint32_t)(dx + 8);
+            ih_off[k] = (uint32_t)dx + g.n[0] * ((uint32_t)dy + g.n[1] * (uint32_t)dz);
         }
     }
     // 3D interpolation, phase B: the LDS byte offsets of the neighbours
@@ -409,6 +471,20 @@ __global__ __launch_bounds__(256) void k_quant(const float* __restrict__ x, Geom
     seg_coords<ND>(lane, lb_lx0, lb_ly, lb_lz);
     const uint32_t lb_rowoff = lb_lx0 + g.n[0] * (lb_ly + g.n[1] * lb_lz);
 
+    // the tiles of this workgroup: every gridDim-th, or where halos read the
+    // neighbouring tiles, one contiguous eighth of the field per XCD
+    // (workgroup mod 8, dispatch order) and every (gridDim / 8)-th of it, so
+    // that a neighbour's lines are still in this XCD's cache (with plain
+    // loads: 26 x 1800 x 3600 values 461 -> 402 us, 512^3 interpolated 453 ->
+    // 447; non-temporal loads keep 454 and 455)
+    uint32_t tile0 = blockIdx.x, tile_end = ntiles, tile_step = gridDim.x;
+    if (kHalo3 && (gridDim.x & 7u) == 0) {
+        const uint32_t per = (ntiles + 7) / 8, xcd = blockIdx.x & 7u;
+        tile_step = gridDim.x >> 3;
+        tile0 = xcd * per + (blockIdx.x >> 3);
+        tile_end = min(ntiles, (xcd + 1) * per);
+    }
+
     // phase-A source of a tile for this lane: first index and real values
     auto tile_src = [&](uint32_t tile, uint32_t& base, uint32_t& nv) {
         const uint32_t bk = tile * kTileBlocks + la_bi;
@@ -420,8 +496,9 @@ __global__ __launch_bounds__(256) void k_quant(const float* __restrict__ x, Geom
     auto tile_load = [&](uint32_t base, uint32_t nv, float v[8]) {
         if (nv == 8 && vec) {
             const f32x4* p = reinterpret_cast<const f32x4*>(x + base);
-            const f32x4 a = __builtin_nontemporal_load(p);
-            const f32x4 c = __builtin_nontemporal_load(p + 1);
+            // (values that neighbouring tiles' halos read stay in the cache)
+            const f32x4 a = kHalo3 ? p[0] : __builtin_nontemporal_load(p);
+            const f32x4 c = kHalo3 ? p[1] : __builtin_nontemporal_load(p + 1);
             v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
             v[4] = c.x; v[5] = c.y; v[6] = c.z; v[7] = c.w;
         } else {
@@ -436,77 +513,97 @@ __global__ __launch_bounds__(256) void k_quant(const float* __restrict__ x, Geom
     uint32_t pf_nv = 0;
     float pf[8];
     // 3D interpolation and global Lorenzo: this thread's halo entries of the
-    // next tile, loaded with its values (raw; bit k of hpm: entry k inside
-    // the field); the origins of the tile's blocks are wave-uniform
+    // next tile, loaded with its values (0, whose q is 0, outside the
+    // field); the origins of the tile's blocks are wave-uniform
     float hpf[kIHPerThread];
-    uint32_t hpm = 0;
     auto halo_load = [&](uint32_t tl) {
         if (!kHalo3) return;
+        const uint32_t bk0 = tl * kTileBlocks;
+        const BlockInfo i0 = block_info(g, tl < tile_end ? bk0 : 0);
+        if (tl < tile_end && i0.bx + kTileBlocks <= g.nb[0] &&
+            (int32_t)(g.n[0] | g.n[1] | g.n[2]) >= 0) {
+            // the tile's blocks lie side by side (uniform; always but at the
+            // end of a row of blocks): an entry is inside the field if none
+            // of its three bytes is below lo (8 at the field's faces, where
+            // the origin is 0) or above hi, all bytes below 128.  (With the
+            // three 64-bit coordinates of every entry, as for the tiles that
+            // wrap, the global kernel ran 530 vector instructions per wave
+            // and tile, now 400; the interpolation one 508 us, now 453.)
+            const uint32_t ox = i0.bx * 8, oy = i0.by * 8, oz = i0.bz * 8;
+            const uint32_t base = ox + g.n[0] * (oy + g.n[1] * oz);
+            const uint32_t lo = (ox ? 0u : 8u) | (oy ? 0u : 8u << 8) | (oz ? 0u : 8u << 16);
+            const uint32_t hi = min(g.n[0] - ox + 7, 127u) | min(g.n[1] - oy + 7, 127u) << 8 |
+                                min(g.n[2] - oz + 7, 127u) << 16;
+            constexpr uint32_t kTop = 0x808080u;
+#pragma unroll
+            for (int k = 0; k < kIHPerThread; k++) {
+                hpf[k] = 0.0f;
+                const uint32_t c = ih_code[k] & 0x7f7f7fu;
+                const bool in = ((((c | kTop) - lo) & ((hi | kTop) - c)) & kTop) == kTop;
+                if (in && t + 256u * k < (uint32_t)kHaloN) hpf[k] = x[base + ih_off[k]];
+            }
+            return;
+        }
         uint32_t ox[kTileBlocks], oy[kTileBlocks], oz[kTileBlocks], valid = 0;
 #pragma unroll
         for (int k = 0; k < kTileBlocks; k++) {
-            const uint32_t bk = tl * kTileBlocks + k;
+            const uint32_t bk = bk0 + k;
             const BlockInfo ik = block_info(g, bk < g.nblocks ? bk : 0);
             ox[k] = ik.bx * 8;
             oy[k] = ik.by * 8;
             oz[k] = ik.bz * 8;
-            valid |= (tl < ntiles && bk < g.nblocks ? 1u : 0u) << k;
+            valid |= (tl < tile_end && bk < g.nblocks ? 1u : 0u) << k;
         }
-        hpm = 0;
 #pragma unroll
         for (int k = 0; k < kIHPerThread; k++) {
             hpf[k] = 0.0f;
             const uint32_t e = t + 256u * k;
-            if (e >= (uint32_t)kHaloN) break;
+            if (e >= (uint32_t)kHaloN) continue;
             const uint32_t hv = ih_code[k];
-            const uint32_t bi = hv & 3u;
+            const uint32_t bi = hv >> 24;
             const uint32_t X0 = bi == 0 ? ox[0] : (bi == 1 ? ox[1] : (bi == 2 ? ox[2] : ox[3]));
             const uint32_t Y0 = bi == 0 ? oy[0] : (bi == 1 ? oy[1] : (bi == 2 ? oy[2] : oy[3]));
             const uint32_t Z0 = bi == 0 ? oz[0] : (bi == 1 ? oz[1] : (bi == 2 ? oz[2] : oz[3]));
-            const int64_t xx = (int64_t)X0 + ((int)((hv >> 2) & 31u) - 8),
-                          yy = (int64_t)Y0 + ((int)((hv >> 7) & 31u) - 8),
-                          zz = (int64_t)Z0 + ((int)((hv >> 12) & 31u) - 8);
+            const int64_t xx = (int64_t)X0 + ((int)(hv & 127u) - 8 * (int)bi - 8),
+                          yy = (int64_t)Y0 + ((int)((hv >> 8) & 127u) - 8),
+                          zz = (int64_t)Z0 + ((int)((hv >> 16) & 127u) - 8);
             if (((valid >> bi) & 1u) && xx >= 0 && yy >= 0 && zz >= 0 && xx < (int64_t)g.n[0] &&
-                yy < (int64_t)g.n[1] && zz < (int64_t)g.n[2]) {
+                yy < (int64_t)g.n[1] && zz < (int64_t)g.n[2])
                 hpf[k] = x[(uint64_t)xx + (uint64_t)g.n[0] * ((uint64_t)yy + (uint64_t)g.n[1] * (uint64_t)zz)];
-                hpm |= 1u << k;
-            }
         }
     };
-    // first tile: workgroup w, or for the 3D interpolation predictor (whose
-    // halo reads the neighbouring tiles) the tiles of one round spread so
-    // that the workgroups of one XCD (w mod 8, dispatch order) take one
-    // contiguous eighth of them
-    uint32_t tile0 = blockIdx.x;
-    if (MODE == kQuantInterp && ND == 3 && (gridDim.x & 7u) == 0)
-        tile0 = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
     {
         uint32_t base = 0;
-        if (tile0 < ntiles) tile_src(tile0, base, pf_nv);
-        tile_load(base, tile0 < ntiles ? pf_nv : 0u, pf);
+        if (tile0 < tile_end) tile_src(tile0, base, pf_nv);
+        tile_load(base, tile0 < tile_end ? pf_nv : 0u, pf);
         halo_load(tile0);
     }
 
-    for (uint32_t tile = tile0; tile < ntiles; tile += gridDim.x) {
+    for (uint32_t tile = tile0; tile < tile_end; tile += tile_step) {
         // ---------------- phase A: prequantise (values loaded a tile ago)
         {
             const uint32_t nv = pf_nv;
             float v[8];
 #pragma unroll
             for (int i = 0; i < 8; i++) v[i] = pf[i];
+            // (a value past the field was loaded as 0, whose q is 0)
             int32_t q[8];
             uint32_t pm = 0;
-            bool bad = false;
+            uint64_t odd = 0;
 #pragma unroll
-            for (int i = 0; i < 8; i++) {
-                bool p;
-                const int32_t qi = prequant1(v[i], e2, inv, eb_abs, p);
-                const bool valid = i < (int)nv;
-                bad |= check_finite && valid && !__builtin_isfinite(v[i]);
-                q[i] = valid ? qi : 0;
-                pm |= (valid && p ? 1u : 0u) << i;
+            for (int i = 0; i < 8; i++) q[i] = fq(v[i], odd);
+            if (odd) {  // uniform
+                bool bad = false;
+#pragma unroll
+                for (int i = 0; i < 8; i++) {
+                    bool p;
+                    q[i] = prequant1(v[i], e2, inv, eb_abs, p);
+                    const bool valid = i < (int)nv;
+                    bad |= check_finite && valid && !__builtin_isfinite(v[i]);
+                    pm |= (valid && p ? 1u : 0u) << i;
+                }
+                if (bad) atomicOr(&misc->flags, F_NONFINITE);
             }
-            if (bad) atomicOr(&misc->flags, F_NONFINITE);
             int4* dst = reinterpret_cast<int4*>(&Q[la_bi * kQStride + la_s * 8]);
             dst[0] = make_int4(q[0], q[1], q[2], q[3]);
             dst[1] = make_int4(q[4], q[5], q[6], q[7]);
@@ -515,25 +612,37 @@ __global__ __launch_bounds__(256) void k_quant(const float* __restrict__ x, Geom
         if (MODE == kQuantInterp && ND == 3) {
             // interpolation (3D): the grid values outside the blocks that
             // the stride-s predictions of the tile read (loaded a tile ago)
+            int32_t hq[kIHPerThread];
+            uint64_t odd = 0;
+#pragma unroll
+            for (int k = 0; k < kIHPerThread; k++) hq[k] = fq(hpf[k], odd);
+            if (odd) {  // uniform
+                bool pq;
+#pragma unroll
+                for (int k = 0; k < kIHPerThread; k++) hq[k] = prequant1(hpf[k], e2, inv, eb_abs, pq);
+            }
 #pragma unroll
             for (int k = 0; k < kIHPerThread; k++) {
                 const uint32_t e = t + 256u * k;
-                if (e >= (uint32_t)(kTileBlocks * kIHB + kIHX)) break;
-                bool pq;
-                const int32_t v = prequant1(hpf[k], e2, inv, eb_abs, pq);
-                HI[e] = ((hpm >> k) & 1u) ? v : 0;
+                if (e < (uint32_t)(kTileBlocks * kIHB + kIHX)) HI[e] = hq[k];
             }
         }
         if (MODE == kQuantGlobal && ND == 3) {
             // global Lorenzo (3D): the grid values just outside the tile's
             // blocks (global_halo_at), loaded a tile ago
+            int32_t hq[kIHPerThread];
+            uint64_t odd = 0;
+#pragma unroll
+            for (int k = 0; k < kIHPerThread; k++) hq[k] = fq(hpf[k], odd);
+            if (odd) {  // uniform
+                bool pq;
+#pragma unroll
+                for (int k = 0; k < kIHPerThread; k++) hq[k] = prequant1(hpf[k], e2, inv, eb_abs, pq);
+            }
 #pragma unroll
             for (int k = 0; k < kIHPerThread; k++) {
                 const uint32_t e = t + 256u * k;
-                if (e >= (uint32_t)kHaloN) break;
-                bool pq;
-                const int32_t v = prequant1(hpf[k], e2, inv, eb_abs, pq);
-                HG[e] = ((hpm >> k) & 1u) ? v : 0;
+                if (e < (uint32_t)kHaloN) HG[e] = hq[k];
             }
         } else if (MODE == kQuantGlobal) {
             for (uint32_t e = t; e < (uint32_t)(kTileBlocks * kHB + kHL); e += 256) {
@@ -585,9 +694,9 @@ __global__ __launch_bounds__(256) void k_quant(const float* __restrict__ x, Geom
         }
         __syncthreads();
         {
-            const uint32_t nt = tile + gridDim.x;
+            const uint32_t nt = tile + tile_step;
             uint32_t base = 0;
-            if (nt < ntiles) tile_src(nt, base, pf_nv);
+            if (nt < tile_end) tile_src(nt, base, pf_nv);
             else pf_nv = 0;
             tile_load(base, pf_nv, pf);
             halo_load(nt);
@@ -925,14 +1034,23 @@ __global__ __launch_bounds__(256) void k_quant(const float* __restrict__ x, Geom
             __syncthreads();
             continue;
         }
-        // codes: residuals in (-512, 512) -> residual + 512, otherwise 0
+        // codes: residual + 512 where that lies in 1..1023, otherwise 0 (so is
+        // residual -512).  A full block (uniform) needs no test per value.
+        const bool full = blk && !__ballot(nv != 8);
         uint32_t code[8];
         uint32_t cmin = 0xFFFFFFFFu;
 #pragma unroll
         for (int i = 0; i < 8; i++) {
-            const uint32_t u = (uint32_t)(d[i] + (kRadius - 1));
-            code[i] = u < (uint32_t)(2 * kRadius - 1) ? u + 1 : 0u;
-            if (i < (int)nv) cmin = min(cmin, code[i]);
+            const uint32_t c = (uint32_t)(d[i] + kRadius);
+            code[i] = c < (uint32_t)(2 * kRadius) ? c : 0u;
+        }
+        if (full) {
+#pragma unroll
+            for (int i = 0; i < 8; i++) cmin = min(cmin, code[i]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; i++)
+                if (i < (int)nv) cmin = min(cmin, code[i]);
         }
         if (MODE == kQuantShuffle && blk) {
             // lane = slots 8 s .. 8 s + 7 of the block (the segment): the
@@ -973,23 +1091,33 @@ __global__ __launch_bounds__(256) void k_quant(const float* __restrict__ x, Geom
         // instead of 1.9 on the 1024^3 fronts/spikes field.)
         if (MODE == kQuantShuffle) {
             // no histogram: the bit-shuffle codec needs none
-        } else if (blk && MODE != kQuantInterp) {
+        } else if (MODE != kQuantInterp) {
             const uint32_t ca = (uint32_t)kRadius;
             uint32_t na = 0;
+            if (full) {
 #pragma unroll
-            for (int i = 0; i < 8; i++) {
-                const bool valid = i < (int)nv;
-                const bool ma = valid && code[i] == ca;
-                na += (uint32_t)__popcll(__ballot(ma));
-                if (valid && !ma) atomicAdd(&H[code[i]], 1u);
+                for (int i = 0; i < 8; i++) {
+                    const bool ma = code[i] == ca;
+                    na += (uint32_t)__popcll(__ballot(ma));
+                    if (!ma) atomicAdd(&H[code[i]], 1u);
+                }
+            } else if (blk) {
+#pragma unroll
+                for (int i = 0; i < 8; i++) {
+                    const bool valid = i < (int)nv;
+                    const bool ma = valid && code[i] == ca;
+                    na += (uint32_t)__popcll(__ballot(ma));
+                    if (valid && !ma) atomicAdd(&H[code[i]], 1u);
+                }
             }
             if (lane == 0 && na) atomicAdd(&H[ca], na);
         } else if (blk) {
             // top-3: residuals -1, 0, 1 by ballots, one add each per wave
             uint32_t nk[3] = {0, 0, 0};
+            const uint32_t vm = (1u << nv) - 1u;
 #pragma unroll
             for (int i = 0; i < 8; i++) {
-                const bool valid = i < (int)nv;
+                const bool valid = (vm >> i) & 1u;
                 const uint32_t k = code[i] - (uint32_t)(kRadius - 1);  // 0, 1, 2 for codes 511..513
 #pragma unroll
                 for (uint32_t j = 0; j < 3; j++) nk[j] += (uint32_t)__popcll(__ballot(valid && k == j));
