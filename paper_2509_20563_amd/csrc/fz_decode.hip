@@ -1262,11 +1262,12 @@ constexpr uint32_t kWaveBlocks = 16384;
 // its last (oidx[b].y), both left at zero for a block without outliers
 // (cleared beforehand); the list must be strictly increasing; the sum of pos_hash
 // over the list for the decode-side check.  Each thread takes groups of 4
-// consecutive entries (one 16-byte load when the list is aligned), its
-// neighbours at the group edges by two scalar loads that hit the cache
-// lines of the adjacent lanes; the workgroup reduces its hash and flag and
+// consecutive entries (one 16-byte load when the list is aligned), four of
+// them in flight, its neighbours at the group edges from the adjacent lanes
+// (the wave's outer two loaded); the workgroup reduces its hash and flag and
 // adds them with one atomic each (few workgroups, so few same-address
-// atomics: these serialise at the memory side).
+// atomics: these serialise at the memory side).  18.6 M entries: 46 us with
+// one group in flight and the edges loaded by every lane, 35 now (63 in 256 workgroups, 39 in 512).
 __device__ __forceinline__ void outlier_entry(uint64_t i, uint32_t p, bool has_prev, uint32_t prev, bool has_next,
                                               uint32_t next, uint32_t nblocks, uint2* __restrict__ oidx, uint64_t& h,
                                               bool& bad) {
@@ -1283,26 +1284,38 @@ __global__ __launch_bounds__(256) void k_outlier_index(const uint32_t* __restric
     const uint32_t t = threadIdx.x;
     const uint64_t stride = (uint64_t)gridDim.x * 256;
     const uint64_t ngroups = (n_out + 3) / 4;
+    const uint32_t lane = t & 63;
+    constexpr int U = 4;
     uint64_t h = 0;
     bool bad = false;
-    for (uint64_t q = (uint64_t)blockIdx.x * 256 + t; q < ngroups; q += stride) {
-        const uint64_t i0 = 4 * q;
-        uint32_t v[4];
-        if (vec && i0 + 4 <= n_out) {
-            const uint4 a = *reinterpret_cast<const uint4*>(opos + i0);
-            v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-        } else {
+    // (uniform over the wave: the lanes exchange their edges)
+    for (uint64_t q = (uint64_t)blockIdx.x * 256 + t; q - lane < ngroups; q += U * stride) {
+        uint32_t v[U][4], edge[U];
 #pragma unroll
-            for (int k = 0; k < 4; k++) v[k] = i0 + k < n_out ? opos[i0 + k] : 0u;
+        for (int u = 0; u < U; u++) {
+            const uint64_t i0 = 4 * (q + u * stride);
+            if (vec && i0 + 4 <= n_out) {
+                const uint4 a = *reinterpret_cast<const uint4*>(opos + i0);
+                v[u][0] = a.x; v[u][1] = a.y; v[u][2] = a.z; v[u][3] = a.w;
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; k++) v[u][k] = i0 + k < n_out ? opos[i0 + k] : 0u;
+            }
+            const uint64_t ie = lane == 0 ? i0 - 1 : i0 + 4;
+            edge[u] = (lane == 0 || lane == 63) && ie < n_out ? opos[ie] : 0u;
         }
-        const uint32_t prev = i0 ? opos[i0 - 1] : 0u;
-        const uint32_t next = i0 + 4 < n_out ? opos[i0 + 4] : 0u;
 #pragma unroll
-        for (int k = 0; k < 4; k++) {
-            const uint64_t i = i0 + k;
-            if (i < n_out)
-                outlier_entry(i, v[k], i > 0, k ? v[k - 1] : prev, i + 1 < n_out, k < 3 ? v[k + 1] : next, nblocks,
-                              oidx, h, bad);
+        for (int u = 0; u < U; u++) {
+            const uint64_t i0 = 4 * (q + u * stride);
+            const uint32_t up = (uint32_t)__shfl_up((int)v[u][3], 1, 64), dn = (uint32_t)__shfl_down((int)v[u][0], 1, 64);
+            const uint32_t prev = lane ? up : edge[u], next = lane < 63 ? dn : edge[u];
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const uint64_t i = i0 + k;
+                if (i < n_out)
+                    outlier_entry(i, v[u][k], i > 0, k ? v[u][k - 1] : prev, i + 1 < n_out, k < 3 ? v[u][k + 1] : next,
+                                  nblocks, oidx, h, bad);
+            }
         }
     }
 #pragma unroll
