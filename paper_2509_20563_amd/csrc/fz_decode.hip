@@ -1422,6 +1422,16 @@ Interior interior_of(const Geom& g) {
     return r;
 }
 
+// LDS of a launch beyond the kernel's own 40 KB, so that two workgroups of
+// the strided 3D decode share a CU and not three (the staged one's registers
+// leave room for two): a lane reads its block's stream 16 bytes at a time and
+// writes 32-byte pieces of rows, and with more waves in flight their lines
+// leave the L2 before they are used up.  Decode stage, us, three workgroups /
+// two: 26 x 1800 x 3600 243/190, 560^3 221/200, no difference at 384^3.
+// (Residuals in strided rows, written by a kernel with fewer registers, go
+// the other way, 271/284; 1D and 2D: no difference.)
+constexpr uint32_t kTwoGroups = 16384;
+
 // Wave-per-block decode of all blocks (edges false) or of those outside
 // the interior.
 template <int MODE>
@@ -1478,8 +1488,9 @@ void launch_decode(hipStream_t st, const Geom& g, const uint32_t* stream, uint64
     if (fast) {
         const uint32_t fg = (I.n + 255) / 256;
 #define FZ_FAST(NDV, V)                                                                                               \
-    hipLaunchKernelGGL((k_decode_fast<NDV, false, V>), dim3(fg), dim3(256), 0, st, g, I.ib[0], I.ib[1], I.n, stream, \
-                       stream_words, off, chunks, lut, oval, oidx, n_out, e2, out, (int32_t*)nullptr, misc, -1,      \
+    hipLaunchKernelGGL((k_decode_fast<NDV, false, V>), dim3(fg), dim3(256), NDV == 3 ? kTwoGroups : 0u, st, g,        \
+                       I.ib[0], I.ib[1], I.n, stream, stream_words, off, chunks, lut, oval, oidx, n_out, e2, out,     \
+                       (int32_t*)nullptr, misc, -1,                                                                   \
                        (const uint8_t*)nullptr, (const uint64_t*)nullptr, (const int32_t*)nullptr, (uint64_t)0)
         if (vec && g.ndim == 3 && I.ib[0] % 64 == 0) {
             // staged row stores where a wave covers one run of 64 blocks
