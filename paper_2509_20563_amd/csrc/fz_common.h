@@ -590,32 +590,29 @@ __device__ __forceinline__ void block_prefix(int32_t (&v)[8], uint32_t lane) {
     }
     // 3D (the whole wave active): y within the 8 lanes of one z by DPP row
     // shifts (lanes whose source lies in the other z of the 16-lane row
-    // masked), then z over lane bits 3-5 by butterflies: the partner's
-    // running total of its 2^k z-levels, lane ^ 8 by a DPP row rotation,
-    // lane ^ 16 and lane ^ 32 by the permlane swaps, added to the prefix of
-    // the lanes in the upper half
+    // masked), then z over lane bits 3-5: the total of the partner's 2^k
+    // z-levels added to the prefix of the lanes in the upper half, lane ^ 8
+    // by DPP row moves, lane ^ 16 and lane ^ 32 by the permlane swaps (which
+    // return own and partner's total, in the upper half the partner's first).
+    // Masks and sums of both in place of selects: 16 instructions a value,
+    // where selects took 27.
     const uint32_t ly = lane & 7;
+    const uint32_t m1 = ly >= 1 ? ~0u : 0u, m2 = ly >= 2 ? ~0u : 0u;
+    const uint32_t m16 = (lane & 16) ? ~0u : 0u, m32 = (lane & 32) ? ~0u : 0u;
 #pragma unroll
     for (int i = 0; i < 8; i++) {
-        // every cross-lane read by all lanes, outside the selects
         uint32_t a = (uint32_t)v[i];
-        const uint32_t y1 = dpp32<0x111, 0xf>(a);
-        a += ly >= 1 ? y1 : 0u;
-        const uint32_t y2 = dpp32<0x112, 0xf>(a);
-        a += ly >= 2 ? y2 : 0u;
-        const uint32_t y4 = dpp32<0x114, 0xf>(a);
-        a += ly >= 4 ? y4 : 0u;
+        a += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a, 0x111, 0xf, 0xf, true) & m1;
+        a += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a, 0x112, 0xf, 0xf, true) & m2;
+        a += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a, 0x114, 0xf, 0xa, false);  // lanes 4-7, 12-15
         uint32_t tot = a;
-        uint32_t o = dpp32<0x128, 0xf>(tot);  // lane ^ 8
-        a += (lane & 8) ? o : 0u;
-        tot += o;
+        a += dpp32<0x118, 0xf>(tot);    // lane - 8, where in the row
+        tot += dpp32<0x128, 0xf>(tot);  // lane ^ 8
         const auto s16 = __builtin_amdgcn_permlane16_swap(tot, tot, false, false);
-        o = (lane & 16) ? s16[0] : s16[1];  // lane ^ 16
-        a += (lane & 16) ? o : 0u;
-        tot += o;
+        a += s16[0] & m16;
+        tot = s16[0] + s16[1];
         const auto s32 = __builtin_amdgcn_permlane32_swap(tot, tot, false, false);
-        o = (lane & 32) ? s32[0] : s32[1];  // lane ^ 32
-        a += (lane & 32) ? o : 0u;
+        a += s32[0] & m32;
         v[i] = (int32_t)a;
     }
 }

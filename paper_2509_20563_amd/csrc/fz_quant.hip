@@ -309,14 +309,12 @@ constexpr int quant_waves(int nd, int mode) {
 }
 
 template <int ND, int MODE>
-__global__ __launch_bounds__(256, quant_waves(ND, MODE)) void k_quant(const float* __restrict__ x, Geom g, uint32_t mode, double eb,
-                                               int vec, Misc* misc, uint32_t* __restrict__ hist_g,
-                                               uint16_t* __restrict__ codes, uint32_t ntiles,
-                                               uint32_t* __restrict__ tile_cnt, uint2* __restrict__ ostage,
-                                               uint2* __restrict__ pstage, int fixed_pred,
-                                               const uint8_t* __restrict__ bpred, int32_t* __restrict__ coef,
-                                               const uint32_t* __restrict__ cw_ref, uint8_t* __restrict__ choice,
-                                               uint32_t* __restrict__ costs) {
+__global__ __launch_bounds__(256, quant_waves(ND, MODE))
+void k_quant(const float* __restrict__ x, Geom g, uint32_t mode, double eb, int vec, Misc* misc,
+             uint32_t* __restrict__ hist_g, uint16_t* __restrict__ codes, uint32_t ntiles,
+             uint32_t* __restrict__ tile_cnt, uint2* __restrict__ ostage, uint2* __restrict__ pstage, int fixed_pred,
+             const uint8_t* __restrict__ bpred, int32_t* __restrict__ coef, const uint32_t* __restrict__ cw_ref,
+             uint8_t* __restrict__ choice, uint32_t* __restrict__ costs) {
     constexpr bool PRED = MODE != kQuantP0 && MODE != kQuantShuffle;
     // bit-shuffle: one block's plane words per wave
     __shared__ uint32_t SW[MODE == kQuantShuffle ? 4 * kShufWords : 1];
