@@ -295,8 +295,8 @@ __device__ __forceinline__ void adam_update(float* __restrict__ w, float* __rest
     w[p] -= lr * (mp / c1) / (sqrtf(vp / c2) + eps);
 }
 
-// Sums of the workgroups' gradient rows, in row order within eight slices
-// and then over the slices; the loss (sum of the squared errors / (3 B));
+// Sums of the workgroups' gradient rows, in double, in row order within
+// eight slices and then over the slices; the loss (sum of the squared errors / (3 B));
 // with A.m also the Adam step.  Thread = (parameter, slice), so that a row
 // of 64 workgroups is eight loads per thread, all in flight: latency-bound
 // (2.9 us).
@@ -304,10 +304,10 @@ constexpr int kRedParams = 32, kRedSlices = 8;
 __global__ __launch_bounds__(256) void k_train_reduce(const float* __restrict__ part, uint32_t rows, uint32_t B,
                                                       float* __restrict__ grad, float* __restrict__ loss,
                                                       double* __restrict__ loss_sum, TrainAdam A, float c1, float c2) {
-    __shared__ float r[kRedSlices][kRedParams];
+    __shared__ double r[kRedSlices][kRedParams];
     const uint32_t t = threadIdx.x, q = t % kRedParams, sl = t / kRedParams;
     const uint32_t p = blockIdx.x * kRedParams + q;
-    float acc = 0.0f;
+    double acc = 0.0;
     if (p <= (uint32_t)kSelectorParams) {
         const uint32_t per = (rows + kRedSlices - 1) / kRedSlices;
         const uint32_t k0 = sl * per, k1 = min(rows, k0 + per);
@@ -319,13 +319,14 @@ __global__ __launch_bounds__(256) void k_train_reduce(const float* __restrict__ 
     if (sl != 0 || p > (uint32_t)kSelectorParams) return;
     acc = ((r[0][q] + r[1][q]) + (r[2][q] + r[3][q])) + ((r[4][q] + r[5][q]) + (r[6][q] + r[7][q]));
     if (p == (uint32_t)kSelectorParams) {
-        const float l = acc / (3.0f * (float)B);
-        if (loss) *loss = l;
+        const double l = acc / (3.0 * (double)B);
+        if (loss) *loss = (float)l;
         if (loss_sum) *loss_sum += l;
         return;
     }
-    grad[p] = acc;
-    if (A.m && p >= (uint32_t)kW1) adam_update(A.w, A.m, A.v, p, acc, A.lr, A.b1, A.b2, A.eps, c1, c2);
+    const float gp = (float)acc;
+    grad[p] = gp;
+    if (A.m && p >= (uint32_t)kW1) adam_update(A.w, A.m, A.v, p, gp, A.lr, A.b1, A.b2, A.eps, c1, c2);
 }
 
 // Adam on the learned parameters; step number t >= 1.
