@@ -297,16 +297,12 @@ __device__ __forceinline__ void global_halo_at(uint32_t e, uint32_t& bi, int& dx
 // kept words in order).
 constexpr int kQuantP0 = 0, kQuantPred = 1, kQuantTrial = 2, kQuantInterp = 3, kQuantGlobal = 4, kQuantShuffle = 5;
 
-// Waves per SIMD the registers have to allow.  The halo of the 3D predictors
-// costs registers: without a bound the interpolation kernel took 170 (two
-// waves per SIMD: 561 us for 512^3 values; 453 at three, 510 at four, which
-// spills), the global one 133 (three: 502 us for 26 x 1800 x 3600; 461 at
-// four, 659 at five).  The others are not bound by it (first-order 3D:
-// 1642 us for 1024^3 values at five waves, 1672 at six with 12 B of spills,
-// 2523 at eight).
-constexpr int quant_waves(int nd, int mode) {
-    return nd != 3 ? 1 : (mode == kQuantInterp ? 3 : (mode == kQuantGlobal ? 4 : 1));
-}
+// Waves per SIMD the registers have to allow.  The 3D interpolation kernel
+// takes 138 for itself (three waves: 436 us for 512^3 values) and fits four
+// without spills (394 us).  The others are left alone: the 3D global one has
+// four (five spill: 659 us against 461 for 26 x 1800 x 3600), the first-order
+// one five (1642 us for 1024^3 values; six 1672, eight 2523, with spills).
+constexpr int quant_waves(int nd, int mode) { return nd == 3 && mode == kQuantInterp ? 4 : 1; }
 
 template <int ND, int MODE>
 __global__ __launch_bounds__(256, quant_waves(ND, MODE))
@@ -526,7 +522,7 @@ void k_quant(const float* __restrict__ x, Geom g, uint32_t mode, double eb, int 
             // the origin is 0) or above hi, all bytes below 128.  (With the
             // three 64-bit coordinates of every entry, as for the tiles that
             // wrap, the global kernel ran 530 vector instructions per wave
-            // and tile, now 400; the interpolation one 508 us, now 453.)
+            // and tile, now 400; the interpolation one 508 us, then 453.)
             const uint32_t ox = i0.bx * 8, oy = i0.by * 8, oz = i0.bz * 8;
             const uint32_t base = ox + g.n[0] * (oy + g.n[1] * oz);
             const uint32_t lo = (ox ? 0u : 8u) | (oy ? 0u : 8u << 8) | (oz ? 0u : 8u << 16);
@@ -557,7 +553,11 @@ void k_quant(const float* __restrict__ x, Geom g, uint32_t mode, double eb, int 
             hpf[k] = 0.0f;
             const uint32_t e = t + 256u * k;
             if (e >= (uint32_t)kHaloN) continue;
-            const uint32_t hv = ih_code[k];
+            uint32_t hv = ih_code[k];
+            // (or the compiler keeps the 64-bit offsets of this rare path in
+            // registers over all tiles, 28 of them: interpolation 447 us and
+            // global 402 where they now take 394 and 385)
+            asm volatile("" : "+v"(hv));
             const uint32_t bi = hv >> 24;
             const uint32_t X0 = bi == 0 ? ox[0] : (bi == 1 ? ox[1] : (bi == 2 ? ox[2] : ox[3]));
             const uint32_t Y0 = bi == 0 ? oy[0] : (bi == 1 ? oy[1] : (bi == 2 ? oy[2] : oy[3]));
