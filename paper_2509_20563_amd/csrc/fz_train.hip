@@ -216,9 +216,12 @@ __global__ __launch_bounds__(256) void k_train_step(const float* __restrict__ w,
             d2[r] = h2[r] > 0.0f ? d : 0.0f;
             D2[(4 * q + r) * kRow + j] = d2[r];
             gb2 += d2[r];
-            g3[0] = __builtin_fmaf(dy.x, h2[r], g3[0]);
-            g3[1] = __builtin_fmaf(dy.y, h2[r], g3[1]);
-            g3[2] = __builtin_fmaf(dy.z, h2[r], g3[2]);
+            // (a sample past the batch has activations too, of the biases
+            // alone: where they overflow, 0 times them would be no number)
+            const float a2 = tile * kTrainTile + 4 * q + r < B ? h2[r] : 0.0f;
+            g3[0] = __builtin_fmaf(dy.x, a2, g3[0]);
+            g3[1] = __builtin_fmaf(dy.y, a2, g3[1]);
+            g3[2] = __builtin_fmaf(dy.z, a2, g3[2]);
             // lanes 0..2 of wave 0's groups: the output biases
             gb3 += u == 0 ? dy.x : (u == 1 ? dy.y : dy.z);
         }
