@@ -969,10 +969,19 @@ __global__ __launch_bounds__(256) void k_inverse_wave(Geom g, const int32_t* __r
 // itself after a few codewords, so 2 to 8 rounds settle nearly every block
 // (28 to 83 codewords one after the other in place of 512, host simulation
 // over Gaussian random fields, waves, noise and positions at 1 to 9.6 bits
-// a value); a round settles at least one more lane whatever the code, so
-// at most 64 are needed.  A scan of the lanes' codeword counts then gives
-// each lane its place, a last pass leaves the residuals in LDS, and lane =
-// segment of 8 values applies the inverse in registers (as k_unshuffle).
+// a value).  A scan of the lanes' codeword counts then gives each lane its
+// place, a last pass leaves the residuals in LDS, and lane = segment of 8
+// values applies the inverse in registers (as k_unshuffle).
+//
+// A code whose codewords are nearly all equally long hardly falls into
+// step: a round settles one more lane, 64 rounds in all (uniform noise under
+// regression, 8 bits a value, 16384 blocks 190-205 us, a lane per block 56).
+// Where many lanes are still unsettled after a few rounds (kWaveCheck,
+// kWaveLeft), or any after many (kWaveRounds), every lane walks its part
+// from each of the kLmax places it can start at, and the true starts follow
+// from part to part: 12 walks more (82-102 us; codes that fall into step
+// within 1 us of where they were.  Every block so after 4 rounds: 81-98 us,
+// but 87 instead of 58 where 8 rounds settle it).
 //
 // It issues about five times the instructions of the lane decoder per
 // block (1250 per wave and 2D block, 62% of the time of 8000 blocks), hence
@@ -981,6 +990,8 @@ __global__ __launch_bounds__(256) void k_inverse_wave(Geom g, const int32_t* __r
 // for the interior and 53 after it for the edges.
 constexpr int kWaveWords = 200;  // 31 + 6144 bits, the codeword across the end, two words of window
 constexpr int kWaveField = 0, kWaveRow = 1, kWavePred = 2;
+constexpr uint32_t kWaveCheck = 4, kWaveRounds = 24;
+constexpr int kWaveLeft = 16;
 
 // The e-th block that is not interior: planes of blocks past ib2, then rows
 // past ib1, then columns past ib0 (at most one of each).
@@ -1092,13 +1103,14 @@ __global__ __launch_bounds__(256) void k_decode_wave(
             const uint64_t hi = (((uint64_t)W[k] << 32) | W[k + 1]) << s;
             return hi | (((uint64_t)W[k + 2] << s) >> 32);
         };
-        // positions count from the first word's first bit
-        const uint32_t S = (T + 63) / 64, end = s0 + T;
-        const uint32_t pend = min(s0 + (lane + 1) * S, end);
-        uint32_t pst = min(s0 + lane * S, end), pe = 0, n = 0;
-        bool todo = true;
-        while (__ballot(todo)) {
-            uint32_t p = todo ? pst : pend;
+        // positions count from the first word's first bit; a part holds the
+        // bits of about 8 values (a thin block has fewer parts: parts of
+        // less than a codeword would settle one per round)
+        const uint32_t parts = min(64u, (nv_blk + 7) / 8);
+        const uint32_t S = parts == 64 ? (T + 63) / 64 : (T + parts - 1) / parts, end = s0 + T;
+        const uint32_t pbeg = min(s0 + lane * S, end), pend = min(s0 + (lane + 1) * S, end);
+        // the codewords from bit p to the part's end: their number; p past them
+        auto walk = [&](uint32_t& p) -> uint32_t {
             uint32_t c = 0;
             while (__ballot(p < pend)) {
                 uint64_t buf = window(min(p, end));
@@ -1113,6 +1125,37 @@ __global__ __launch_bounds__(256) void k_decode_wave(
                     c += act ? 1u : 0u;
                 }
             }
+            return c;
+        };
+        uint32_t pst = pbeg, pe = 0, n = 0, round = 0;
+        bool todo = true;
+        while (const uint64_t left = __ballot(todo)) {
+            if ((round == kWaveCheck && __popcll(left) > kWaveLeft) || round == kWaveRounds) {
+                // a code that hardly falls into step: the part's end from
+                // each of the kLmax places it can start at (4 bits per
+                // place), followed from part to part; the next walk, from
+                // the starts so found, is the last
+                uint64_t ends = 0;
+#pragma unroll 1
+                for (uint32_t k = 0; k < (uint32_t)kLmax; k++) {
+                    uint32_t p = pbeg + k;
+                    walk(p);
+                    ends |= (uint64_t)(p - pend) << (4 * k);
+                }
+                uint32_t k = 0, mine = 0;
+#pragma unroll 8
+                for (uint32_t l = 0; l < 64; l++) {
+                    mine = lane == l ? k : mine;
+                    const uint64_t el = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(ends >> 32), (int)l) << 32 |
+                                        (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)ends, (int)l);
+                    k = (uint32_t)(el >> (4 * k)) & 15u;
+                }
+                pst = pbeg + mine;
+                todo = true;
+            }
+            round++;
+            uint32_t p = todo ? pst : pend;
+            const uint32_t c = walk(p);
             if (todo) {
                 pe = p;
                 n = c;
