@@ -9,6 +9,8 @@
 //                    Lorenzo), dequantisation, row stores - codes never
 //                    leave registers
 //   k_patch        - lossless patches written over the reconstruction
+#include <algorithm>
+
 #include "fz_common.h"
 #include "fz_kernels.h"
 
@@ -979,19 +981,21 @@ __global__ __launch_bounds__(256) void k_inverse_wave(Geom g, const int32_t* __r
 // Where many lanes are still unsettled after a few rounds (kWaveCheck,
 // kWaveLeft), or any after many (kWaveRounds), every lane walks its part
 // from each of the kLmax places it can start at, and the true starts follow
-// from part to part: 12 walks more (82-102 us; codes that fall into step
-// within 1 us of where they were.  Every block so after 4 rounds: 81-98 us,
-// but 87 instead of 58 where 8 rounds settle it).
+// from part to part: 12 walks more (79-100 us; codes that fall into step
+// within 1 us of where they were, but for some at 1000 blocks, 28 -> 38.
+// Every block so after 4 rounds: 81-98 us, but 87 instead of 58 where 8 rounds
+// settle it.  Walks from no further than the longest codeword: no gain,
+// such codes have rare codewords of 12 bits).
 //
 // It issues about five times the instructions of the lane decoder per
 // block (1250 per wave and 2D block, 62% of the time of 8000 blocks), hence
-// the rule of launch_wave's callers (kWaveBlocks).  A 1800 x 3600 field
+// the rules of wave_decode.  A 1800 x 3600 field
 // (12769 blocks, 449 at the edges): 48 us, where the lane decoders took 48
 // for the interior and 53 after it for the edges.
 constexpr int kWaveWords = 200;  // 31 + 6144 bits, the codeword across the end, two words of window
 constexpr int kWaveField = 0, kWaveRow = 1, kWavePred = 2;
-constexpr uint32_t kWaveCheck = 4, kWaveRounds = 24;
-constexpr int kWaveLeft = 16;
+constexpr uint32_t kWaveCheck = 3, kWaveRounds = 24;
+constexpr int kWaveLeft = 24;
 
 // The e-th block that is not interior: planes of blocks past ib2, then rows
 // past ib1, then columns past ib0 (at most one of each).
@@ -1104,10 +1108,11 @@ __global__ __launch_bounds__(256) void k_decode_wave(
             return hi | (((uint64_t)W[k + 2] << s) >> 32);
         };
         // positions count from the first word's first bit; a part holds the
-        // bits of about 8 values (a thin block has fewer parts: parts of
-        // less than a codeword would settle one per round)
-        const uint32_t parts = min(64u, (nv_blk + 7) / 8);
-        const uint32_t S = parts == 64 ? (T + 63) / 64 : (T + parts - 1) / parts, end = s0 + T;
+        // bits of at least a value (with parts of less than a codeword a
+        // round settles one; parts of 4 values or more: 73 instead of 69 us
+        // for 160 x 161 x 162 values)
+        const uint32_t parts = min(64u, nv_blk);
+        const uint32_t S = parts == 64u ? (T + 63) / 64 : (T + parts - 1) / parts, end = s0 + T;
         const uint32_t pbeg = min(s0 + lane * S, end), pend = min(s0 + (lane + 1) * S, end);
         // the codewords from bit p to the part's end: their number; p past them
         auto walk = [&](uint32_t& p) -> uint32_t {
@@ -1304,12 +1309,6 @@ __global__ __launch_bounds__(256) void k_decode_wave(
     outlier_totals(t, true, oq, 0, misc, reinterpret_cast<uint32_t*>(LUT));
 }
 
-// Blocks a wave-per-block launch takes at most.  Measured, decode of a 3D
-// field alone (us, lane per block / wave per block): at 1e-2 512 blocks 46 /
-// 12, 4096 47 / 17, 13824 47 / 34, 21952 47 / 47; at 2e-4, with blocks of
-// outliers, 82 / 32, 81 / 30, 80 / 64, 80 / 84.
-constexpr uint32_t kWaveBlocks = 16384;
-
 // ------------------------------------------------------ outlier block index
 // Per block, the list index of its first outlier (oidx[b].x) and one past
 // its last (oidx[b].y), both left at zero for a block without outliers
@@ -1449,20 +1448,75 @@ void launch_reset_lut(hipStream_t st, Misc* misc, uint32_t* hist, uint64_t* d1, 
 }
 
 namespace {
-// Full blocks per axis (the fast kernels' domain).
+// Full blocks per axis (the fast kernels' domain); the longest chain of
+// values a lane follows in one block of the field, and in one outside the
+// interior (rows along x count as multiples of 8); and whether only the
+// slowest axis is cut, so that the blocks outside are the last ones.
 struct Interior {
     uint32_t ib[3];
     uint32_t n;
+    uint32_t longest, edge_longest;
+    bool edge_last;
 };
 Interior interior_of(const Geom& g) {
     Interior r;
     uint64_t n = 1;
-    for (int a = 0; a < 3; a++) {
-        r.ib[a] = a < (int)g.ndim ? g.n[a] / g.bs[a] : 1u;
+    r.longest = 1;
+    r.edge_longest = 0;
+    r.edge_last = true;
+    for (int a = 0; a < (int)g.ndim; a++) {
+        const uint32_t full = g.bs[a], cut = g.n[a] % full;
+        auto row = [&](uint32_t v) { return a == 0 ? (v + 7) & ~7u : v; };
+        r.ib[a] = g.n[a] / full;
         n *= r.ib[a];
+        r.longest *= row(std::min(g.n[a], full));
+        r.edge_longest = std::max(r.edge_longest, row(cut) * ((uint32_t)kBlockElems / full));
+        if (cut && a + 1 < (int)g.ndim) r.edge_last = false;
     }
+    for (int a = (int)g.ndim; a < 3; a++) r.ib[a] = 1;
     r.n = (uint32_t)n;
     return r;
+}
+
+// Whether a wave per block decodes the field.  A lane per block takes 45-60
+// us for full blocks however many there are (one lane's chain, so less in
+// proportion for shorter ones), the wave about 10 us and then in proportion to
+// the blocks, to their bits and to the blocks with outliers.  Measured, decode
+// stage of Gaussian random fields and uniform noise at 1 to 9.7 bits a value,
+// 512 to 24576 blocks, us, wave / lane:
+//   1D 16384 blocks at 1.3 bits 33/49, 12288 at 3.5 with an outlier a block
+//      49/47 (16384 54/48), at 6.4 46/47; 8192 at 8.7 36/46
+//   2D 16384 at 4.1 44/47, at 6.9 46/47; 12288 at 9.3 45/47; with an outlier
+//      a block 8192 at 7.3 44/47, 12288 52/48
+//   3D 16250 at 7.8 46/47; with outliers 8320 at 9.6 50/60, 16250 69/60;
+//      interpolation residuals 12480 at 6.3 39/44, 16250 50/44
+//   regression: 1D 8192 at 8.5 65/56, 4096 45/55; 2D 12288 at 5.8 49/55, 3D
+//      12480 at 7.0 35/55; codes that do not fall into step (8 bits) 8192 blocks
+//      1D 63/55, 2D 47/55, 3D 49/55, 12288 81/56, 64/56, 64/55
+//   blocks of 32 values (1 x 400000) 22-71/13-17, of 64 (1 x 1000 x 1000)
+//      35-71/18, of 96 (3 x 500000) 25-86/23-34, of 256 (4 x 1000 x 1000)
+//      33-52/46, rows of 4 (1000 x 1000 x 4) 32-50/83
+// `after`: what the lane decode takes beyond the fast kernel's time, in halves
+// of it: kernels for the edges (1801 x 3601 values at 8.6 bits and 22%
+// outliers: wave 68, interior and edges 90), or the general kernel for a field
+// without an interior (15 x 500000 values 72/133).
+// Many outliers add a half too: 3D 16250 blocks with 27% 74/78.
+constexpr uint32_t kWaveBlocks = 16384;
+bool wave_decode(const Geom& g, const Interior& I, uint64_t words, uint64_t n_out, bool regression, uint32_t after) {
+    const uint32_t blocks = I.longest >= 256 ? kWaveBlocks : 48 * I.longest;
+    const uint64_t load = words + 48 * std::min(n_out, (uint64_t)g.nblocks);
+    const uint64_t most = g.ndim > 1 ? 28u << 16 : (regression ? 15u << 16 : 20u << 16);
+    const uint32_t dense = n_out > 16ull * g.nblocks ? 1 : 0;
+    return g.nblocks <= blocks && load <= most * (2 + after + dense) / 2 * I.longest / kBlockElems;
+}
+// Whether it decodes the blocks outside the interior.  Lanes: blocks of few
+// values that are the last ones take little, others wait in every workgroup
+// for one lane.  After the interior, us, wave / lane: 17 x 400000 values
+// (12500 blocks of 32) 12-87/9-17; 9 x 800 x 800 (10000 of 64) 30-50/14;
+// 12 x 800 x 800 (10000 of 256) 23-36/42; 497 x 497 x 498 (11907 of 64 to 128,
+// on three faces) 110 less than lanes; 500^3 20/120.
+bool wave_decode_edges(const Geom& g, const Interior& I) {
+    return g.nblocks - I.n <= (I.edge_last && I.edge_longest < 256 ? 48 * I.edge_longest : kWaveBlocks);
 }
 
 // LDS of a launch beyond the kernel's own 40 KB, so that two workgroups of
@@ -1522,7 +1576,8 @@ void launch_decode(hipStream_t st, const Geom& g, const uint32_t* stream, uint64
                    const int32_t* oval, const uint2* oidx, uint64_t n_out, double e2, float* out,
                    int vec, Misc* misc) {
     const Interior I = interior_of(g);
-    if (g.nblocks <= kWaveBlocks) {
+    const uint32_t after = I.n ? (I.n < g.nblocks ? 1 : 0) : (I.longest > 256 ? 2 : 0);
+    if (wave_decode(g, I, stream_words, n_out, false, after)) {
         launch_wave<kWaveField>(st, g, I, false, stream, stream_words, off, chunks, lut, opos, oval, oidx, n_out, e2,
                                 out, vec, misc);
         return;
@@ -1556,7 +1611,7 @@ void launch_decode(hipStream_t st, const Geom& g, const uint32_t* stream, uint64
 #undef FZ_FAST
     }
     if (fast && I.n == g.nblocks) return;
-    if (g.nblocks - I.n <= kWaveBlocks) {
+    if (fast && wave_decode_edges(g, I)) {
         launch_wave<kWaveField>(st, g, I, true, stream, stream_words, off, chunks, lut, opos, oval, oidx, n_out, e2,
                                 out, vec, misc);
         return;
@@ -1566,9 +1621,9 @@ void launch_decode(hipStream_t st, const Geom& g, const uint32_t* stream, uint64
 #define FZ_GEN(NDV)                                                                                                 \
     hipLaunchKernelGGL(k_decode<NDV>, dim3(grid), dim3(256), 0, st, g, stream, stream_words, off, chunks, lut, opos, \
                        oval, oidx, n_out, e2, out, vec, misc, skip, I.ib[0], I.ib[1], I.ib[2])
+    // (1D: one block at most is cut, a wave's)
     if (g.ndim == 3) FZ_GEN(3);
-    else if (g.ndim == 2) FZ_GEN(2);
-    else FZ_GEN(1);
+    else FZ_GEN(2);
 #undef FZ_GEN
 }
 
@@ -1582,7 +1637,12 @@ void launch_decode_pred(hipStream_t st, const Geom& g, const uint32_t* stream, u
                         int fixed_pred, const uint8_t* bpred, const uint64_t* reg_idx, const int32_t* coefs,
                         uint64_t nreg, double e2, float* out, int vec, Misc* misc) {
     const Interior I = interior_of(g);
-    if (g.nblocks <= kWaveBlocks) {
+    // (where most blocks are second-order, or differ, there is no limit on the
+    // stream: full blocks take a wave 47-75 us at 16384, lanes 55-83 and the
+    // inverse after them; edges in lanes cost two kernels more than the
+    // interior alone)
+    const bool regression = fixed_pred == 2 || (fixed_pred < 0 && 2 * nreg > g.nblocks);
+    if (wave_decode(g, I, regression ? stream_words : 0, regression ? n_out : 0, regression, I.n < g.nblocks ? 4 : 0)) {
         launch_wave<kWavePred>(st, g, I, false, stream, stream_words, off, chunks, lut, opos, oval, oidx, n_out, e2,
                                out, vec, misc, fixed_pred, bpred, reg_idx, coefs, nreg);
         return;
@@ -1640,7 +1700,7 @@ void launch_decode_residuals(hipStream_t st, const Geom& g, const uint32_t* stre
     // stores where a wave covers one run of 64 blocks along x)
     const Interior I = interior_of(g);
     float* rf = reinterpret_cast<float*>(res);
-    if (g.nblocks <= kWaveBlocks) {
+    if (wave_decode(g, I, stream_words, n_out, false, I.n < g.nblocks ? (I.n ? 1 : 2) : 0)) {
         launch_wave<kWaveRow>(st, g, I, false, stream, stream_words, off, chunks, lut, opos, oval, oidx, n_out, 0.0,
                               rf, vec, misc);
         return;
@@ -1665,7 +1725,7 @@ void launch_decode_residuals(hipStream_t st, const Geom& g, const uint32_t* stre
 #undef FZ_ARGS
     }
     if (I.n == g.nblocks) return;
-    if (g.nblocks - I.n <= kWaveBlocks) {
+    if (I.n && wave_decode_edges(g, I)) {
         launch_wave<kWaveRow>(st, g, I, true, stream, stream_words, off, chunks, lut, opos, oval, oidx, n_out, 0.0,
                               rf, vec, misc);
         return;
