@@ -109,6 +109,7 @@ struct BatchSide {
 struct fz_ctx {
     int device = 0;
     int n_cu = 256;
+    uint32_t peers = 1;  // chains of the batch this context is one of
     Misc* misc = nullptr;
     Misc* h_misc = nullptr;  // pinned
     uint8_t* h_hdr = nullptr;  // pinned, 128 B
@@ -682,7 +683,8 @@ int decompress_prepare(fz_ctx* c, const Parsed& r) {
 // Every stage of one decompression (no host synchronisation).
 void decompress_tasks(fz_ctx* c, const Parsed& r, const uint8_t* in, float* d_out, TaskList& T) {
     const MiscIds M(c->misc);
-    const Geom g = r.g;
+    Geom g = r.g;
+    g.peers = c->peers;
     if (r.verbatim) {
         T.push_back({"copy", {{in, ACC_R}, {d_out, ACC_W}},
                      [=](hipStream_t st) { launch_copy(st, in + kHdr, d_out, g.N); }});
@@ -1876,6 +1878,7 @@ int fz_decompress_batch(fz_ctx* c, uint32_t n, const void* d_in, const uint64_t*
         fork_chains(c, s, K);
         for (int k = 0; k < K; k++)
             for (uint32_t i : chains[k]) {
+                s.kids[k]->peers = (uint32_t)K;
                 decompress_enqueue(s.kids[k], r[i], in + h_offsets[i], d_out[i], s.kstream[k], false);
                 if (!r[i].verbatim) launch_field_record(s.kstream[k], s.kids[k]->misc, 0, s.rec + 5ull * i, 1);
             }

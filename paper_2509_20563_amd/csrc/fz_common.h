@@ -122,6 +122,7 @@ struct Geom {
     uint32_t nblocks;
     uint64_t N;
     FastDiv dnb0, dnb1;  // division by nb[0] and nb[1]
+    uint32_t peers;      // fields worked on side by side (a batch's chains); 0 or 1: this one alone
 };
 
 // Block coordinates and real extents of block b.

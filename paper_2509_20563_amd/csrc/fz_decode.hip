@@ -1501,13 +1501,25 @@ Interior interior_of(const Geom& g) {
 // outliers: wave 68, interior and edges 90), or the general kernel for a field
 // without an interior (15 x 500000 values 72/133).
 // Many outliers add a half too: 3D 16250 blocks with 27% 74/78.
+//
+// In a batch (g.peers fields side by side) the lanes of several 3D fields run
+// together where a wave per block fills the chip with one, so these change
+// earlier unless lanes take three kernels (`after` of 4); in 1D and 2D, where
+// the lanes' stores are strided, fields change later.  Whole batches of 8
+// chains, us, wave / lane: 32 x 128^3 at 7.9 bits 666/752, with outliers at 12.9
+// 1050/1047; 32 x 136^3 at 7.9 705/781, at 12.6 1160/1102; 24 x 152^3 at 4.5
+// 598/621, at 7.9 661/639; 16 x 192^3 at 7.8 689/495, second order 891/1212;
+// 26 x 1800 x 3600 at 24 1973/2054; 30 x 6144000 at 6 1249/1408.
 constexpr uint32_t kWaveBlocks = 16384;
 bool wave_decode(const Geom& g, const Interior& I, uint64_t words, uint64_t n_out, bool regression, uint32_t after) {
-    const uint32_t blocks = I.longest >= 256 ? kWaveBlocks : 48 * I.longest;
+    const bool batch = g.peers > 1, early = batch && g.ndim == 3 && after < 4;
+    const uint32_t full = early ? 6400 : kWaveBlocks;
+    const uint32_t blocks = I.longest >= 256 ? full : std::min(full, 48 * I.longest);
     const uint64_t load = words + 48 * std::min(n_out, (uint64_t)g.nblocks);
-    const uint64_t most = g.ndim > 1 ? 28u << 16 : (regression ? 15u << 16 : 20u << 16);
-    const uint32_t dense = n_out > 16ull * g.nblocks ? 1 : 0;
-    return g.nblocks <= blocks && load <= most * (2 + after + dense) / 2 * I.longest / kBlockElems;
+    const uint64_t most = early ? 11u << 16 : (g.ndim > 1 ? 28u << 16 : (regression ? 15u << 16 : 20u << 16));
+    if (!early && n_out > 16ull * g.nblocks) after++;
+    if (batch && g.ndim < 3) after++;
+    return g.nblocks <= blocks && load <= most * (2 + after) / 2 * I.longest / kBlockElems;
 }
 // Whether it decodes the blocks outside the interior.  Lanes: blocks of few
 // values that are the last ones take little, others wait in every workgroup
@@ -1642,7 +1654,8 @@ void launch_decode_pred(hipStream_t st, const Geom& g, const uint32_t* stream, u
     // inverse after them; edges in lanes cost two kernels more than the
     // interior alone)
     const bool regression = fixed_pred == 2 || (fixed_pred < 0 && 2 * nreg > g.nblocks);
-    if (wave_decode(g, I, regression ? stream_words : 0, regression ? n_out : 0, regression, I.n < g.nblocks ? 4 : 0)) {
+    const uint32_t after = fixed_pred == 1 || I.n < g.nblocks ? 4 : 0;
+    if (wave_decode(g, I, regression ? stream_words : 0, regression ? n_out : 0, regression, after)) {
         launch_wave<kWavePred>(st, g, I, false, stream, stream_words, off, chunks, lut, opos, oval, oidx, n_out, e2,
                                out, vec, misc, fixed_pred, bpred, reg_idx, coefs, nreg);
         return;
