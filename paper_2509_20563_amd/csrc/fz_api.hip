@@ -271,7 +271,7 @@ int ensure(fz_ctx* c, const Geom& g) {
     if (e == hipSuccess) e = grow(c->tlast, c->tlast_cap, ntiles);
     if (e == hipSuccess) e = grow(c->desc_cnt, c->desc_cnt_cap, sd_tiles);
     // look-back descriptors of the Huffman encoder's groups
-    if (e == hipSuccess) e = grow(c->desc_bits, c->desc_bits_cap, encode_groups((uint32_t)ntiles));
+    if (e == hipSuccess) e = grow(c->desc_bits, c->desc_bits_cap, encode_descriptors((uint32_t)ntiles));
     if (e == hipSuccess) e = grow(c->desc_chunks, c->desc_chunks_cap, sd_blocks);
     if (e == hipSuccess) e = grow(c->off, c->off_cap, nb);
     if (e == hipSuccess) e = grow(c->oidx, c->oidx_cap, nb);

@@ -750,13 +750,6 @@ void launch_codebook(hipStream_t st, uint32_t* hist, uint8_t* out_lens, uint32_t
     hipLaunchKernelGGL(k_codebook, dim3(1), dim3(1024), 0, st, hist, out_lens, cw, misc);
 }
 
-// Tiles per group: a group's tiles are worked off one after the other, so a
-// field with few tiles is split further.  Measured, 3D fields (us, 12 per
-// group / this rule): 128 tiles 19.1 / 10.7, 1024 20.6 / 14.6, 3456 24.1 /
-// 21.1, 8192 30.1 / 30.4; 1 and 2 per group 17.2 and 15.3 at 1024 tiles, 33
-// and 24 at 3456 (the look-back chain grows with the groups).
-static uint32_t encode_tiles(uint32_t ntiles) { return ntiles >= 6144 ? 8u : (ntiles >= 256 ? 4u : 1u); }
-
 void launch_encode(hipStream_t st, int grid, const uint16_t* codes, const Geom& g, const uint32_t* cw, Misc* misc,
                    uint32_t ntiles, uint8_t* out, uint64_t* desc, uint64_t* tile_start, uint32_t* tfirst,
                    uint32_t* tlast) {

@@ -38,7 +38,25 @@ void launch_codebook(hipStream_t st, uint32_t* hist, uint8_t* out_lens, uint32_t
 void launch_encode(hipStream_t st, int grid, const uint16_t* codes, const Geom& g, const uint32_t* cw, Misc* misc,
                    uint32_t ntiles, uint8_t* out, uint64_t* desc, uint64_t* tile_start, uint32_t* tfirst,
                    uint32_t* tlast);
+// Tiles per group: a group's tiles are worked off one after the other, so a
+// field with few tiles is split further.  Measured, 3D fields (us, 12 per
+// group / this rule): 128 tiles 19.1 / 10.7, 1024 20.6 / 14.6, 3456 24.1 /
+// 21.1, 8192 30.1 / 30.4; 1 and 2 per group 17.2 and 15.3 at 1024 tiles, 33
+// and 24 at 3456 (the look-back chain grows with the groups).
+constexpr uint32_t kEncFew = 256, kEncMany = 6144;
+inline uint32_t encode_tiles(uint32_t ntiles) { return ntiles >= kEncMany ? 8u : (ntiles >= kEncFew ? 4u : 1u); }
+// Groups of a field, one look-back descriptor each.
 uint32_t encode_groups(uint32_t ntiles);
+// Descriptors of any field of up to ntiles tiles (a field just below a step
+// of encode_tiles has more groups than one above it), so that scratch sized
+// for a field holds for every smaller one.
+inline uint32_t encode_descriptors(uint32_t ntiles) {
+    auto groups = [](uint32_t n) { return (n + encode_tiles(n) - 1) / encode_tiles(n); };
+    uint32_t most = groups(ntiles);
+    for (const uint32_t step : {kEncFew, kEncMany})
+        if (ntiles >= step && groups(step - 1) > most) most = groups(step - 1);
+    return most;
+}
 void launch_finalize(hipStream_t st, const Geom& g, uint32_t mode, double eb, uint32_t pred, Misc* misc,
                      uint8_t* out, uint32_t ntiles, const uint64_t* tile_start, const uint32_t* tfirst,
                      const uint32_t* tlast, const uint32_t* tile_cnt, const uint64_t* tile_off, const uint2* ostage,
