@@ -55,7 +55,7 @@ MODES = (("lorenzo1", 0), ("selector", 3), ("trial", 4))
 STAGE_KERNEL = {
     "compress:minmax": ("fz::k_minmax", "fz_quant.hip"),
     "compress:quant": ("fz::k_quant<3, 0>", "fz_quant.hip"),
-    "compress:encode": ("fz::k_encode<3>", "fz_huffman.hip"),
+    "compress:encode": ("fz::k_encode<3, 8u>", "fz_huffman.hip"),
     "compress:finalize": ("fz::k_finalize", "fz_huffman.hip"),
     "decompress:oindex": ("fz::k_outlier_index", "fz_decode.hip"),
     "decompress:decode": ("fz::k_decode_fast<3, false, true, true, false, false>", "fz_decode.hip"),

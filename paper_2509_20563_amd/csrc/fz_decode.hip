@@ -8,6 +8,8 @@
 //                    outlier overwrite, in-block prefix sums (inverse
 //                    Lorenzo), dequantisation, row stores - codes never
 //                    leave registers
+//   k_decode_wave  - one wave per block, for fields and sets of edge blocks
+//                    too small for a lane per block (wave_decode)
 //   k_patch        - lossless patches written over the reconstruction
 #include <algorithm>
 

@@ -428,6 +428,8 @@ constexpr uint64_t kGlDeep = 131072;
 // per axis / segments:
 //   2D always: 1800 x 3600 234/36, 500 x 500 60/18, 3600 x 64 230/39,
 //     64 x 3600 22/18
+//     (whole calls of long, narrow fields, a serial chain either way:
+//     20000 x 200 2401/226, 100000 x 40 10017/720, 2000000 x 3 93537/12575)
 //   3D, enough waves (2048 full ones) to walk z inside k_gl_out: 26 x 1800 x 3600
 //     903/497 (256^3 would take 938 so: 4 us a plane, one after the other)
 //   3D, fewer: a z pass first, then k_gl_out takes every plane on its own:

@@ -470,7 +470,12 @@ void k_quant(const float* __restrict__ x, Geom g, uint32_t mode, double eb, int 
     // (workgroup mod 8, dispatch order) and every (gridDim / 8)-th of it, so
     // that a neighbour's lines are still in this XCD's cache (with plain
     // loads: 26 x 1800 x 3600 values 461 -> 402 us, 512^3 interpolated 453 ->
-    // 447; non-temporal loads keep 454 and 455)
+    // 447; non-temporal loads keep 454 and 455).  Fetched by the whole
+    // kernel, before this and the shorter halo addressing / now: 26 x 1800 x
+    // 3600 global 1.81 / 1.00 GB, 512^3 global 1.20 / 0.66, interpolated 1.01 /
+    // 0.82.  At 1024^3 an eighth's planes no longer fit the caches: global 9.8 /
+    // 9.4 GB, interpolated 9.8 / 13.4 (2.46 / 1.97 and 4.04 / 3.16 ms all the
+    // same).
     uint32_t tile0 = blockIdx.x, tile_end = ntiles, tile_step = gridDim.x;
     if (kHalo3 && (gridDim.x & 7u) == 0) {
         const uint32_t per = (ntiles + 7) / 8, xcd = blockIdx.x & 7u;

@@ -1,10 +1,11 @@
 // Training of the block-feature selector network on the device: targets,
 // feature standardisation, forward pass, backpropagation and Adam (Kingma
 // and Ba).  Not part of compression or decompression; the network it
-// produces is used by the selector mode of the compressor.  fp32
-// throughout; sums over a minibatch run in a fixed order, so a run is
-// repeatable on one device, but training is not meant to be bit-exact
-// across machines (a given parameter set is).
+// produces is used by the selector mode of the compressor.  Activations,
+// gradients of 16 samples and Adam are fp32; the sums over a minibatch's
+// workgroups, the losses and the feature statistics are double.  All run in a
+// fixed order, so a run is repeatable on one device, but training is not meant
+// to be bit-exact across machines (a given parameter set is).
 #include "fz_common.h"
 #include "fz_kernels.h"
 
@@ -346,7 +347,7 @@ void launch_targets(hipStream_t st, const uint32_t* costs, uint64_t n, float* t)
     if (grid) hipLaunchKernelGGL(k_targets, dim3((uint32_t)grid), dim3(256), 0, st, costs, n, t);
 }
 
-// w is followed by the scratch of the partial sums (train_w_bytes).
+// w is followed by the scratch of the partial sums (kTrainWBytes).
 void launch_feature_stats(hipStream_t st, const float* feat, uint64_t n, float* w) {
     uint64_t parts = (n + 127) / 128;
     if (parts > kFeatureParts) parts = kFeatureParts;

@@ -63,7 +63,7 @@ THIN = [(4096, 3, 260), (1, 1000, 1000), (4, 1000, 1000), (1000, 1000, 4), (9, 8
         (1, 400000), (1, 40000), (3, 500000), (15, 300000), (17, 200000), (300000, 5), (70000, 33), (7, 7, 40000)]
 
 
-@pytest.mark.parametrize("pred", [0, 1, 2, 4, 5, 6])
+@pytest.mark.parametrize("pred", [0, 2, 4, 6])
 @pytest.mark.parametrize("shape", THIN)
 def test_thin(fz, ctx, shape, pred):
     _check(ctx, _rough(shape, 4), 1e-3, pred)
@@ -73,5 +73,3 @@ def test_thin(fz, ctx, shape, pred):
 @pytest.mark.parametrize("shape", [(9_000_000,), (2896, 3008), (208, 216, 208), (512, 64, 520), (40, 48, 56)])
 def test_unaligned_output(fz, ctx, shape, pred):
     _check(ctx, _rough(shape, 5), 1e-3, pred, at=1)
-    if shape == (208, 216, 208):
-        _check(ctx, _rough(shape, 5), 1e-2, pred, at=3)

@@ -19,8 +19,8 @@ def ctx(fz):
 
 
 @pytest.mark.parametrize("shape", SHAPES)
-@pytest.mark.parametrize("levels", [128, 250, 256, 260, 300])
-@pytest.mark.parametrize("pred", [0, 2, 5])
+@pytest.mark.parametrize("levels", [128, 256, 300])
+@pytest.mark.parametrize("pred", [0, 2])
 def test_equally_long_codewords(fz, ctx, shape, levels, pred):
     # residuals (nearly) uniform over `levels` values: steps along x for the
     # first-order predictor, the values themselves for the other two
